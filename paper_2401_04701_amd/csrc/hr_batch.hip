@@ -143,7 +143,7 @@ bool hr_instance_shape(hr_instance& in, size_t elems[2], size_t* lds_bytes)
         in.blocks = (in.n + T - 1) / T;
         elems[0] = in.n;
         elems[1] = 0;
-        *lds_bytes = 0;
+        *lds_bytes = labelprop_lds_words(HR_WORKER_THREADS) * 4;
         break;
     }
     default:

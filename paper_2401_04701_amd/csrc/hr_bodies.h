@@ -85,12 +85,117 @@ __device__ void reduce_body(const hr_env& e, const G& gin, const G& gout,
     }
 }
 
-// One logical block (T threads, vertices lb*T .. lb*T+T) of label
-// propagation: l = atomic load of label[v]; for every edge (v, u) an atomic
+// Label propagation, one logical thread per vertex v (thread v % T of logical
+// block v / T): l = atomic load of label[v]; for every edge (v, u) an atomic
 // min of l into label[u], or for a seeded edge a plain read and plain write
-// of label[u].  grp / gcol: optional monitoring of the CSR reads (shadow
-// null when off).
-template <int CHECK, bool PAIRS = false, class G = hr_gref>
+// of label[u].  grp / gcol: optional monitoring of the CSR reads (shadow null
+// when off).  Two physical forms of the same accesses; this one:
+//
+// The hardware block takes the nv consecutive vertices v0 .. v0+nv, loads
+// their labels and row pointers (one lane per vertex), and after a block
+// barrier all its lanes walk the vertices' edges, which are consecutive in
+// CSR, whichever vertex they belong to.  An edge is checked with the identity
+// of its vertex's logical thread (block and thread index, found by a search
+// of the row pointers in LDS), so the accesses and their happens-before are
+// the program's; the hardware barrier is no barrier of the program.  A
+// logical thread's edges then run side by side on several lanes: the job has
+// no barrier, so all its accesses lie in one epoch, where the order of one
+// thread's updates does not change a summary (step and merge take them as one
+// thread's).  An atomic min that would not lower the label is only its atomic
+// load (the same access class and the same value): the hubs' labels are hot,
+// and memory-side atomics on one line run one after another.
+//
+// What bounds it: random requests past the L2, a label and a shadow word per
+// edge (about 22 G requests/s here), and for small graphs the block that
+// holds the largest hub.  R-MAT of 2^22 vertices and 2^25 edges: 3.0 ms per
+// checked launch against 45.7 ms with one lane per vertex (a hub's lane walks
+// tens of thousands of edges, a round trip each), and 7.0 ms with every
+// atomic min performed.  One edge per lane at a time, in 64 registers (two
+// 1024-thread blocks per compute unit), was as fast as 2 or 4 edges per lane
+// (3.2 and 3.3 ms, with more registers) and as loading the next edge's words
+// ahead (3.0 ms, the small graph slower).
+template <int CHECK, class G>
+__device__ __forceinline__ void labelprop_edges(const hr_env& e, const G& glab, const G& grp,
+                                                const G& gcol, int32_t* __restrict__ label,
+                                                const int32_t* __restrict__ rp,
+                                                const int32_t* __restrict__ col,
+                                                const uint8_t* __restrict__ mask, uint32_t n,
+                                                uint32_t T, uint32_t v0, uint32_t nv, uint32_t* lds)
+{
+    int32_t* s_rp = (int32_t*)lds;               // nv + 1 row pointers
+    int32_t* s_l = s_rp + nv + 1;                // labels
+    uint32_t* s_id = (uint32_t*)(s_l + nv);      // logical block << 10 | thread
+    for (uint32_t i = threadIdx.x; i < nv; i += blockDim.x) {
+        const uint32_t v = v0 + i, lb = v / T, t = v - lb * T;
+        hr_thread th{};
+        if constexpr (CHECK) {
+            th = hr_thread_make(e, lb, t);
+            s_id[i] = lb << 10 | t;
+        }
+        const typename G::word q = hr_gload<CHECK>(th, glab, v);
+        const int32_t l = __hip_atomic_load(label + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t r = rp[v];
+        if (i + 1 == nv) s_rp[nv] = rp[v + 1];
+        const typename G::pend p = hr_gi<2, CHECK, true>(e, th, glab, v, HR_SITE_LP_OWN, q);
+        s_l[i] = l;
+        s_rp[i] = r;
+        hr_gs<2, CHECK>(e, th, glab, p, v, HR_SITE_LP_OWN);
+        if (CHECK && grp.shadow) {
+            hr_g<0, CHECK>(e, th, grp, v, HR_SITE_LP_CSR);
+            hr_g<0, CHECK>(e, th, grp, v + 1, HR_SITE_LP_CSR);
+        }
+    }
+    __syncthreads();
+    const int64_t e1 = s_rp[nv];
+    for (int64_t k = (int64_t)s_rp[0] + threadIdx.x; k < e1; k += blockDim.x) {
+        const uint32_t u = (uint32_t)col[k];
+        const bool seeded = mask[k];
+        typename G::word w = 0;
+        if constexpr (CHECK) w = hr_gload<CHECK>(hr_thread_of(e, 0, 0), gcol, (uint64_t)k);
+        // the edge's vertex: the last i with s_rp[i] <= k
+        uint32_t lo = 0, hi = nv;
+        while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (s_rp[mid] <= k) lo = mid;
+            else hi = mid;
+        }
+        const int32_t l = s_l[lo];
+        hr_thread th{};
+        if constexpr (CHECK) th = hr_thread_of(e, s_id[lo] >> 10, s_id[lo] & 1023u);
+        typename G::word q = 0;
+        typename G::pend pu{}, pc{};
+        int32_t cur = 0;
+        if (u < n) {
+            q = hr_gload<CHECK>(th, glab, u);
+            cur = __hip_atomic_load(label + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (CHECK && gcol.shadow)
+            pc = hr_gi<0, CHECK, true>(e, th, gcol, (uint64_t)k, HR_SITE_LP_CSR, w);
+        if (u < n && !seeded) {
+            if (cur > l) atomicMin(label + u, l);
+            pu = hr_gi<2, CHECK, true>(e, th, glab, u, HR_SITE_LP_MIN, q);
+        }
+        if (CHECK && gcol.shadow)
+            hr_gs<0, CHECK>(e, th, gcol, pc, (uint64_t)k, HR_SITE_LP_CSR);
+        hr_gs<2, CHECK>(e, th, glab, pu, u, HR_SITE_LP_MIN);
+        if (u < n && seeded) {
+            const int32_t r = label[u];
+            hr_gpre<0, CHECK, false>(e, th, glab, u, HR_SITE_LP_SEED_READ, q);
+            label[u] = r < l ? r : l;
+            hr_g<1, CHECK>(e, th, glab, u, HR_SITE_LP_SEED_WRITE);
+        }
+    }
+}
+
+// LDS words labelprop_edges needs for nv vertices.
+constexpr uint32_t labelprop_lds_words(uint32_t nv) { return 3 * nv + 1; }
+
+// The other form: one lane per logical thread, vertices lb*T .. lb*T+T, one
+// edge at a time.  For contexts with wave grouping, whose hook instructions
+// must run one logical wave per hardware wave (hr_group).  While edge k is
+// checked, the column index of edge k+2, and the seeded flag of edge k+1 and
+// the shadow word of its target, are already in flight.
+template <int CHECK, class G = hr_gref>
 __device__ void labelprop_body(const hr_env& e, const G& glab, const G& grp, const G& gcol,
                                int32_t* __restrict__ label, const int32_t* __restrict__ rp,
                                const int32_t* __restrict__ col, const uint8_t* __restrict__ mask,
@@ -107,85 +212,6 @@ __device__ void labelprop_body(const hr_env& e, const G& glab, const G& grp, con
         hr_g<0, CHECK>(e, th, grp, v, HR_SITE_LP_CSR);
         hr_g<0, CHECK>(e, th, grp, v + 1, HR_SITE_LP_CSR);
     }
-    if constexpr (!CHECK) {
-        // the plain kernel: nothing to hide, the simple loop is its fastest form
-        for (int32_t k = e0; k < e1; ++k) {
-            const uint32_t u = (uint32_t)col[k];
-            if (u >= n) continue;
-            if (mask[k]) {
-                const int32_t r = label[u];
-                label[u] = r < l ? r : l;
-            } else {
-                atomicMin(label + u, l);
-            }
-        }
-        return;
-    }
-    if (PAIRS && !e.group) {
-        // Edges in pairs, for the long lists of hub vertices whose threads
-        // bound the launch: the exchanges of both edges of a pair are in
-        // flight together and settled after both are issued, while the
-        // column indices of the pair after next and the seeded flags and
-        // shadow words of the next pair are loaded.  (It takes more
-        // registers than the batch and serving workers, which inline every
-        // workload body, can give; they run the one-edge loop below.)
-        const auto col_at = [&](int32_t q) { return q < e1 ? (uint32_t)col[q] : 0u; };
-        uint32_t a0 = col_at(e0), b0 = col_at(e0 + 1), a1 = col_at(e0 + 2), b1 = col_at(e0 + 3);
-        typename G::word sa = e0 < e1 ? hr_gload<CHECK>(th, glab, a0) : 0;
-        typename G::word sb = e0 + 1 < e1 ? hr_gload<CHECK>(th, glab, b0) : 0;
-        uint8_t ma = e0 < e1 ? mask[e0] : 0, mb = e0 + 1 < e1 ? mask[e0 + 1] : 0;
-        for (int32_t k = e0; k < e1; k += 2) {
-            const uint32_t a2 = col_at(k + 4), b2 = col_at(k + 5);
-            const typename G::word na = k + 2 < e1 ? hr_gload<CHECK>(th, glab, a1) : 0;
-            const typename G::word nb = k + 3 < e1 ? hr_gload<CHECK>(th, glab, b1) : 0;
-            const uint8_t nma = k + 2 < e1 ? mask[k + 2] : 0, nmb = k + 3 < e1 ? mask[k + 3] : 0;
-            const uint32_t ua = a0, ub = b0;
-            const typename G::word qa = sa, qb = sb;
-            const uint8_t fa = ma, fb = mb;
-            const bool two = k + 1 < e1;
-            a0 = a1;
-            b0 = b1;
-            a1 = a2;
-            b1 = b2;
-            sa = na;
-            sb = nb;
-            ma = nma;
-            mb = nmb;
-            if (gcol.shadow) {
-                hr_g<0, CHECK>(e, th, gcol, (uint64_t)k, HR_SITE_LP_CSR);
-                if (two) hr_g<0, CHECK>(e, th, gcol, (uint64_t)k + 1, HR_SITE_LP_CSR);
-            }
-            typename G::pend pa{}, pb{};
-            if (ua < n) {
-                if (fa) {
-                    const int32_t r = label[ua];
-                    hr_gpre<0, CHECK>(e, th, glab, ua, HR_SITE_LP_SEED_READ, qa);
-                    label[ua] = r < l ? r : l;
-                    hr_g<1, CHECK, true>(e, th, glab, ua, HR_SITE_LP_SEED_WRITE);
-                } else {
-                    atomicMin(label + ua, l);
-                    pa = hr_gi<2, CHECK, true>(e, th, glab, ua, HR_SITE_LP_MIN, qa);
-                }
-            }
-            if (two && ub < n) {
-                if (fb) {
-                    const int32_t r = label[ub];
-                    hr_gpre<0, CHECK>(e, th, glab, ub, HR_SITE_LP_SEED_READ, qb);
-                    label[ub] = r < l ? r : l;
-                    hr_g<1, CHECK, true>(e, th, glab, ub, HR_SITE_LP_SEED_WRITE);
-                } else {
-                    atomicMin(label + ub, l);
-                    pb = hr_gi<2, CHECK, true>(e, th, glab, ub, HR_SITE_LP_MIN, qb);
-                }
-            }
-            hr_gs<2, CHECK>(e, th, glab, pa, ua, HR_SITE_LP_MIN);
-            hr_gs<2, CHECK>(e, th, glab, pb, ub, HR_SITE_LP_MIN);
-        }
-        return;
-    }
-    // One edge at a time.  While edge k is checked, the
-    // column index of edge k+2, and the seeded flag of edge k+1 and the
-    // shadow word of its target, are already in flight.
     uint32_t u0 = e0 < e1 ? (uint32_t)col[e0] : 0u;
     uint32_t u1 = e0 + 1 < e1 ? (uint32_t)col[e0 + 1] : 0u;
     typename G::word s0 = e0 < e1 ? hr_gload<CHECK>(th, glab, u0) : 0;

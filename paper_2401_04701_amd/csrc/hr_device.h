@@ -156,6 +156,21 @@ __device__ __forceinline__ void hr_set_flag(const hr_env& e, uint32_t bit)
     __hip_atomic_fetch_or(e.ctr + HR_CTR_FLAGS, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The checker state of a logical thread in its first epoch, for a lane that
+// checks accesses on its behalf (hr_thread_make has run for it elsewhere).
+__device__ __forceinline__ hr_thread hr_thread_of(const hr_env& e, uint32_t block, uint32_t thread)
+{
+    hr_thread t;
+    t.block = block;
+    t.thread = thread;
+    t.bc = 0;
+    t.wc = 0;
+    t.enabled = 1;
+    t.gid = hr::g::pack_id(e.launch, block, thread, 0, 0);
+    t.lid = hr::l::pack_id(thread, 0, 0);
+    return t;
+}
+
 // A 4-byte word keeps block ids and thread indices modulo its field widths:
 // two accessors whose ids fold together look like one, which can hide a race
 // between them.  The first lane of each wave with such a thread raises the
@@ -169,14 +184,7 @@ __device__ __noinline__ void hr_fold_flag(uint32_t* ctr)
 __device__ __forceinline__ hr_thread hr_thread_make(const hr_env& e, uint32_t block,
                                                     uint32_t thread)
 {
-    hr_thread t;
-    t.block = block;
-    t.thread = thread;
-    t.bc = 0;
-    t.wc = 0;
-    t.enabled = 1;
-    t.gid = hr::g::pack_id(e.launch, block, thread, 0, 0);
-    t.lid = hr::l::pack_id(thread, 0, 0);
+    const hr_thread t = hr_thread_of(e, block, thread);
     if (e.word4) {
         const bool folded = (block & ~hr::c::block_mask(e.word4)) != 0 ||
                             (thread & ~hr::c::thread_mask(e.word4)) != 0;

@@ -99,9 +99,16 @@ __device__ __forceinline__ void run_item(const hr_env& e, const hr_inst_dev& I, 
         if (I.pattern == HR_PAT_LABELPROP) {
             using G = hr_gref_1d;
             const G none{};
-            labelprop_body<1, false, G>(e, G{I.g0}, none, none, (int32_t*)I.p0,
-                                        (const int32_t*)I.p1, (const int32_t*)I.p2,
-                                        (const uint8_t*)I.p3, I.n, T, lb, t);
+            if (e.group) {   // uniform: an environment field
+                labelprop_body<1>(e, G{I.g0}, none, none, (int32_t*)I.p0, (const int32_t*)I.p1,
+                                  (const int32_t*)I.p2, (const uint8_t*)I.p3, I.n, T, lb, t);
+            } else {
+                const uint32_t vb = I.pack * T, v0 = item * vb;
+                labelprop_edges<1>(
+                    e, G{I.g0}, none, none, (int32_t*)I.p0, (const int32_t*)I.p1,
+                    (const int32_t*)I.p2, (const uint8_t*)I.p3, I.n, T, v0, min(vb, I.n - v0),
+                    smem);
+            }
         }
     }
 }

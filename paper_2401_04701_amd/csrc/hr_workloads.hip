@@ -66,16 +66,32 @@ __global__ __launch_bounds__(1024) void k_reduce(hr_kargs a, hr_gref gin, hr_gre
                        drop, (int32_t*)smem, smem + n, 0);
 }
 
-template <int CHECK>
-__global__ __launch_bounds__(1024) void k_labelprop(hr_kargs a, hr_gref glab, hr_gref grp,
-                                                    hr_gref gcol, int32_t* __restrict__ label,
+// One lane per vertex (contexts with wave grouping).
+template <int CHECK, class R, class G>
+__global__ __launch_bounds__(1024) void k_labelprop(hr_kargs a, R glab, R grp, R gcol,
+                                                    int32_t* __restrict__ label,
                                                     const int32_t* __restrict__ rp,
                                                     const int32_t* __restrict__ col,
                                                     const uint8_t* __restrict__ mask, uint32_t n)
 {
-    using G = hr_gref_1d;
-    labelprop_body<CHECK, true, G>(a.env, G{glab}, G{grp}, G{gcol}, label, rp, col, mask, n,
-                                   blockDim.x, blockIdx.x, threadIdx.x);
+    labelprop_body<CHECK>(a.env, G{glab}, G{grp}, G{gcol}, label, rp, col, mask, n, blockDim.x,
+                          blockIdx.x, threadIdx.x);
+}
+
+// Blocks of consecutive vertices whose edges all lanes walk (labelprop_edges);
+// tpb: threads per logical block, vb: vertices per hardware block.
+template <int CHECK, class R, class G>
+__global__ __launch_bounds__(1024, 8) void k_labelprop_edges(hr_kargs a, R glab, R grp, R gcol,
+                                                          int32_t* __restrict__ label,
+                                                          const int32_t* __restrict__ rp,
+                                                          const int32_t* __restrict__ col,
+                                                          const uint8_t* __restrict__ mask,
+                                                          uint32_t n, uint32_t tpb, uint32_t vb)
+{
+    extern __shared__ uint32_t smem[];
+    const uint32_t v0 = blockIdx.x * vb;
+    labelprop_edges<CHECK, G>(a.env, G{glab}, G{grp}, G{gcol}, label, rp, col, mask, n, tpb,
+                              v0, min(vb, n - v0), smem);
 }
 
 // The checked kernels on 4-byte shadow words.
@@ -89,18 +105,6 @@ __global__ __launch_bounds__(1024) void k_reduce4(hr_kargs a, hr_gref4 gin, hr_g
     using G = hr_gref4_1d<0>;
     reduce_body<CHECK>(a.env, G{gin}, G{gout}, in, out, n, blockDim.x, blockIdx.x, threadIdx.x,
                        drop, (int32_t*)smem, smem + n, 0);
-}
-
-template <int CHECK = 1>
-__global__ __launch_bounds__(1024) void k_labelprop4(hr_kargs a, hr_gref4 glab, hr_gref4 grp,
-                                                     hr_gref4 gcol, int32_t* __restrict__ label,
-                                                     const int32_t* __restrict__ rp,
-                                                     const int32_t* __restrict__ col,
-                                                     const uint8_t* __restrict__ mask, uint32_t n)
-{
-    using G = hr_gref4_1d<0>;
-    labelprop_body<CHECK, true, G>(a.env, G{glab}, G{grp}, G{gcol}, label, rp, col, mask, n,
-                                   blockDim.x, blockIdx.x, threadIdx.x);
 }
 
 // ----------------------------------------------------------- interpreter
@@ -406,6 +410,40 @@ extern "C" hr_status hr_labelprop_check(hr_ctx c, uint32_t r_label, uint32_t r_r
                                mask_dev, n, tpb, hr_stream(c, stream));
 }
 
+// Vertices per 1024-thread block: about 4,096 blocks (8 rounds of the resident
+// ones), within 32..256 (up to 1,024 above 2^30 vertices).  Fewer vertices spread the hubs over more blocks,
+// each of which costs a launch slot and a label round: 100,003 vertices take
+// 0.25 ms per checked launch with 32 vertices, 0.36 ms with 256; 2^22
+// vertices 3.8 ms with 32 and 3.0 ms with 256 (3.6 ms with 512).
+static uint32_t labelprop_vertices_per_block(uint32_t n)
+{
+    uint32_t vb = 32;
+    while (vb < 256 && n / vb > 4096) vb *= 2;
+    while ((n - 1) / vb + 1 >= (1u << 22)) vb *= 2;   // a grid holds below 2^32 threads
+    return vb;
+}
+
+// check: 0 plain, 1 checked, 2 checked with the access log.
+template <class R, class G>
+static hr_status launch_labelprop(int check, const hr_kargs& a, R glab, R grp, R gcol,
+                                  int32_t* label, const int32_t* rp, const int32_t* col,
+                                  const uint8_t* mask, uint32_t n, uint32_t tpb, hipStream_t s)
+{
+    if (a.env.group) {
+        auto k = check == 2 ? k_labelprop<2, R, G> : k_labelprop<1, R, G>;
+        HR_LAUNCH(k, dim3((n + tpb - 1) / tpb), dim3(tpb), 0, s, a, glab, grp, gcol, label, rp, col,
+                  mask, n);
+        return HR_OK;
+    }
+    const uint32_t vb = labelprop_vertices_per_block(n);
+    auto k = check == 0   ? k_labelprop_edges<0, R, G>
+             : check == 1 ? k_labelprop_edges<1, R, G>
+                          : k_labelprop_edges<2, R, G>;
+    HR_LAUNCH(k, dim3((n - 1) / vb + 1), dim3(1024), labelprop_lds_words(vb) * 4, s, a, glab, grp,
+              gcol, label, rp, col, mask, n, tpb, vb);
+    return HR_OK;
+}
+
 hr_status hr_launch_labelprop(const hr_kargs& a, uint32_t r_label, uint32_t r_row_ptr,
                               uint32_t r_col, int32_t* label_dev, const int32_t* row_ptr_dev,
                               const int32_t* col_dev, const uint8_t* mask_dev, uint32_t n,
@@ -418,20 +456,16 @@ hr_status hr_launch_labelprop(const hr_kargs& a, uint32_t r_label, uint32_t r_ro
     const bool log = a.env.log != nullptr;
     if (a.env.word4) {
         const hr_gref4 none{nullptr, 0, 0};
-        HR_LAUNCH(log ? k_labelprop4<2> : k_labelprop4<1>, dim3((n + tpb - 1) / tpb), dim3(tpb),
-                  0, s, a, gref4(a, r_label),
-                  r_row_ptr != UINT32_MAX ? gref4(a, r_row_ptr) : none,
-                  r_col != UINT32_MAX ? gref4(a, r_col) : none, label_dev, row_ptr_dev, col_dev,
-                  mask_dev, n);
-        return HR_OK;
+        return launch_labelprop<hr_gref4, hr_gref4_1d<0>>(
+            log ? 2 : 1, a, gref4(a, r_label), r_row_ptr != UINT32_MAX ? gref4(a, r_row_ptr) : none,
+            r_col != UINT32_MAX ? gref4(a, r_col) : none, label_dev, row_ptr_dev, col_dev, mask_dev,
+            n, tpb, s);
     }
     const hr_gref none{nullptr, 0, 0};
-    HR_LAUNCH(log ? k_labelprop<2> : k_labelprop<1>, dim3((n + tpb - 1) / tpb), dim3(tpb), 0, s,
-              a, gref(a, r_label),
-              r_row_ptr != UINT32_MAX ? gref(a, r_row_ptr) : none,
-              r_col != UINT32_MAX ? gref(a, r_col) : none, label_dev, row_ptr_dev, col_dev,
-              mask_dev, n);
-    return HR_OK;
+    return launch_labelprop<hr_gref, hr_gref_1d>(
+        log ? 2 : 1, a, gref(a, r_label), r_row_ptr != UINT32_MAX ? gref(a, r_row_ptr) : none,
+        r_col != UINT32_MAX ? gref(a, r_col) : none, label_dev, row_ptr_dev, col_dev, mask_dev, n,
+        tpb, s);
 }
 
 extern "C" hr_status hr_labelprop_plain(int32_t* label_dev, const int32_t* row_ptr_dev,
@@ -440,10 +474,9 @@ extern "C" hr_status hr_labelprop_plain(int32_t* label_dev, const int32_t* row_p
 {
     if (!label_dev || !row_ptr_dev || !col_dev || !mask_dev || !labelprop_shape_ok(n, tpb))
         return HR_E_INVAL;
-    hr_kargs a{};
-    HR_LAUNCH(k_labelprop<0>, dim3((n + tpb - 1) / tpb), dim3(tpb), 0, (hipStream_t)stream, a,
-              hr_gref{}, hr_gref{}, hr_gref{}, label_dev, row_ptr_dev, col_dev, mask_dev, n);
-    return HR_OK;
+    return launch_labelprop<hr_gref, hr_gref_1d>(0, hr_kargs{}, hr_gref{}, hr_gref{}, hr_gref{},
+                                                 label_dev, row_ptr_dev, col_dev, mask_dev, n, tpb,
+                                                 (hipStream_t)stream);
 }
 
 extern "C" hr_status hr_program_check(hr_ctx c, const uint32_t* regions_host, uint32_t n_regions,
