@@ -378,6 +378,7 @@ extern "C" hr_status hr_batch_run(hr_batch b, const hr_batch_tuning* tune, void*
         hr_fill32(b->d_cursor, 1, s) != hipSuccess)
         return HR_E_HIP;
     hr_env e = hr_make_env(c);
+    e.excl = 1;         // the arena is this run's, and a job's phases are ordered
     e.site_limit = 0;   // site ids are per job; the limit does not apply to a batch
     if (t.coalesce) e.group = t.coalesce == 1 ? 0u : t.coalesce;
     if (t.variant == 0)

@@ -75,8 +75,10 @@ struct hr_env {
     hr_access_rec* log;                 // access log (debug), or null; only
                                         // written while count is not null
     uint32_t log_cap;
-    uint32_t nested;                    // 1: tiles of 2^wave_bits lanes nested in
+    uint16_t nested;                    // 1: tiles of 2^wave_bits lanes nested in
                                         // waves (the hr_tn hooks of hr_nested.h)
+    uint16_t excl;                      // 1: no other kernel touches this kernel's
+                                        // shadow words while it runs
 };
 
 // Shadow layout of a region (the address-to-shadow map): the element at row

@@ -139,6 +139,16 @@ HR_HD constexpr uint64_t step(uint64_t old, uint64_t id, uint32_t k, uint64_t wm
     return mk(T_ST, cl | k, cb | k, cw | k) | (id & keep_t);
 }
 
+// The transitions of an access of class k and identity id and, with others,
+// of accesses of class k by other blocks, on a word that holds neither an
+// access of id's launch nor a race.  False: another case.
+HR_HD bool fresh(uint64_t old, uint64_t id, uint32_t k, bool others, uint64_t* nw)
+{
+    const uint32_t tag = (uint32_t)(old & TAG_M);
+    *nw = others ? (mk(T_MB, 0, k, 0) | (id & LA_M)) : (mk(T_ST, k, k, k) | id);
+    return tag != T_RACE && (tag == T_INIT || ((old ^ id) & LA_M)) && !(others && k == CL_X);
+}
+
 // ---------------------------------------------------------------------------
 // The same transition as a flat table (the paper's encoding of its machine,
 // Sec. IV-B: an array indexed by the old state and the transition labels).
@@ -491,6 +501,14 @@ HR_HD uint32_t step(uint32_t old, uint32_t id, uint32_t k, uint32_t wm, uint32_t
     return st_num(cl | k, cb | k, cw | k) | (id & keep_t);
 }
 
+// As g::fresh (a word without an access of this launch is the initial word;
+// id's block field differs from the other blocks').
+HR_HD bool fresh(uint32_t old, uint32_t id, uint32_t k, bool others, uint32_t* nw)
+{
+    *nw = others ? 1u + k : (st_num(k, k, k) | id);
+    return old == 0 && !(others && k == CL_X);
+}
+
 HR_HD uint32_t merge(uint32_t x, uint32_t y, uint64_t wm, uint32_t lay)
 {
     return narrow(g::merge(widen(x, lay), widen(y, lay), wm), lay);
@@ -542,6 +560,19 @@ HR_HD uint32_t step(uint32_t old, uint32_t id, uint32_t k, uint32_t wm = WAVE_M)
     if (tag == T_MT) return conflicts(cw, k) ? race : old;
     if (d & lm) return conflicts(cw, k) ? race : (mk(T_MT, cb, k) | (id & keep_w));
     return mk(T_ST, cb | k, cw | k) | (id & keep_t);
+}
+
+// The transitions of an access of class k and identity id and of further
+// ones of class k and id's clocks (others 0: none, 1: by other threads of
+// id's group, 2: by threads of other groups too), on a word that holds
+// neither an access of id's block epoch nor a race.  False: another case.
+HR_HD bool fresh(uint32_t old, uint32_t id, uint32_t k, uint32_t others, uint32_t wm, uint32_t* nw)
+{
+    const uint32_t tag = old & TAG_M;
+    *nw = others == 0   ? (mk(T_ST, k, k) | id)
+          : others == 1 ? (mk(T_MT, k, k) | (id & (BC_M | wm | WC_M)))
+                        : (mk(T_MW, k, 0) | (id & BC_M));
+    return tag != T_RACE && (tag == T_INIT || ((old ^ id) & BC_M)) && !(others && k == CL_X);
 }
 }  // namespace l
 

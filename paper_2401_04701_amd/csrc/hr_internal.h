@@ -45,7 +45,22 @@ struct hr_ctx_s {
     uint32_t launch_seq;             // launches since the job started
     uint64_t shadow_bytes;           // live shadow memory
     std::vector<hr_race> carried;    // global races recovered before a shadow clear
+    // Launches of the current epoch (hr_epoch_enter): whether there are any,
+    // the stream of the last, whether several streams or the caller's own
+    // kernels (hr_dev_args) may take part, and whether one of them runs with
+    // env.excl.
+    bool epoch_used = false, epoch_shared = false, epoch_excl = false;
+    hipStream_t epoch_stream = nullptr;
 };
+
+// Account for a checked launch on `s` in the current launch epoch.  *excl
+// (may be NULL: the kernel does not use it) receives the launch's env.excl:
+// every checked launch of the epoch so far was made on `s`, so none runs
+// beside it, and a later one will not either, since a launch on another
+// stream (or hr_dev_args) first waits here for the exclusive ones.  Not
+// granted while `s` is being captured (a graph may be launched anywhere),
+// nor on the per-thread stream, whose handle names several streams.
+hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl);
 
 // Bytes of the counter words at the start of a context's counter-and-ring
 // allocation (the ring follows, 256-byte aligned).

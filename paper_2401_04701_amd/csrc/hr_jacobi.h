@@ -11,18 +11,9 @@
 constexpr uint32_t JACOBI_TILE = 18;
 constexpr uint32_t JACOBI_TILE_WORDS = JACOBI_TILE * JACOBI_TILE;
 
-// One 16x16 tile (logical block lb of a grid nbx tiles wide) of the 5-point
-// sweep u_new = 0.2 (c + n + s + w + e), staged through an 18x18 LDS tile.
-// seeds: NULL or per-block (side << 8 | offset) entries (-1: none); a seeded
-// block's edge thread also writes the neighbour-owned halo cell.
-// ONE_HALO: the halo reads are checked in one hook section per wave (the
-// standalone kernels); without it, in two (the batch and serving workers,
-// which inline every workload body under one register budget: the proxy
-// lanes' second identity would spill there).
 // The synchronization of a tile's threads in jacobi_body: the hardware
-// block's barrier, with the LDS shadow cleared in the body.
+// block's barrier.
 struct hr_block_sync {
-    static constexpr bool CLEARS = true;   // the body clears its LDS shadow
     template <int CHECK>
     __device__ __forceinline__ void bar(const hr_env& e, hr_thread& t) { hr_bar<CHECK>(e, t); }
 };
@@ -30,15 +21,14 @@ struct hr_block_sync {
 // The synchronization of the 256 threads (4 waves) of one tile when a
 // hardware block runs several tiles side by side: a barrier of those waves
 // alone, on an arrival counter in LDS, so that a tile's waves do not wait
-// for the other tiles' slowest wave.  The kernel clears the LDS shadow and
-// the counter, then passes one block barrier, before the body runs.  Every
+// for the other tiles' slowest wave.  The kernel clears the counter, then
+// passes one block barrier, before the body runs.  Every
 // wave of the tile reaches each barrier (the body's barriers are not under
 // divergent control), and all are resident with their block, so the wait
 // ends; it is bounded all the same, and a wait that runs out is reported as
 // a stall (HR_DEVF_STALL) and goes on.  For the checker it is the tile's
 // block barrier: it advances the block clock as hr_barrier_block does.
 struct hr_tile_sync {
-    static constexpr bool CLEARS = false;
     static constexpr uint32_t SPIN_LIMIT = 1u << 22;
     uint32_t* arrive;     // the tile's counter in LDS, zero before the body
     uint32_t target;      // arrivals that end the next barrier
@@ -71,172 +61,181 @@ struct hr_tile_sync {
     }
 };
 
-template <int CHECK, class G = hr_gref, bool ONE_HALO = false, class SYNC = hr_block_sync>
+// One 16x16 tile (logical block lb of a grid nbx tiles wide) of the 5-point
+// sweep u_new = 0.2 (c + n + s + w + e), staged through an 18x18 LDS tile.
+// seeds: NULL or per-block (side << 8 | offset) entries (-1: none); a seeded
+// block's edge thread also writes the neighbour-owned halo cell.
+//
+// Which threads access an element is fixed by the code, so each cell's thread
+// applies all accesses to its shadow words (owner updates): to the old cell's
+// word its own read and the halo reads of the blocks beside an edge cell, to
+// the new cell's word its own write and a neighbour's seeded write of it, to
+// the LDS tile's words the staging writes and then every read of them.  Each
+// global word is loaded once, with the data, and stored once.
+//
+// What bounds it: memory.  4096 x 4096: 0.150 ms per launch, 4.5 TB/s of the
+// 671 MB of grids and shadow words (a large copy reaches 4.9 TB/s here),
+// against 0.278 ms with every access published by its own thread's exchange
+// (100 memory-side requests per tile, which run at 25 G/s on the chip, and
+// 530 vector instructions per wave).  The general transitions in place of
+// the closed forms (hr_own_fast), with their rare paths inside the kernel
+// and not at its end, took 0.184 ms, issue-bound; plain, nontemporal or
+// coherent loads and stores of the words made no difference.
+template <int CHECK, class G = hr_gref, class SYNC = hr_block_sync>
 __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
                             const float* __restrict__ uo, float* __restrict__ un, uint32_t ny,
                             uint32_t nx, uint32_t nbx, const int32_t* __restrict__ seeds,
                             uint32_t lb, uint32_t t, float* tile, uint32_t* tsh, uint32_t lds_id,
                             SYNC sync = SYNC{})
 {
-    constexpr uint32_t TW = JACOBI_TILE_WORDS, TL = JACOBI_TILE;
+    constexpr uint32_t TL = JACOBI_TILE;
     const uint32_t tx = t & 15u, ty = (t >> 4) & 15u;
     const uint32_t bx = lb % nbx, by = lb / nbx;
     const uint32_t gx = bx * 16u + tx, gy = by * 16u + ty;
     const bool inside = t < 256 && gx < nx && gy < ny;
+    uint32_t late = 0;        // owner updates left to the end (bits below)
+    constexpr uint32_t OLD = 1, CENTRE = 2, ROW = 4, COL = 8, NEW = 16;
     hr_thread th{};
-    if constexpr (CHECK) {
-        th = hr_thread_make(e, lb, t);
-        if constexpr (SYNC::CLEARS) {
-            if (t < 256)
-                for (uint32_t i = t; i < TW; i += 256) tsh[i] = 0;
-            __syncthreads();
-        }
-    }
+    if constexpr (CHECK) th = hr_thread_make(e, lb, t);
     const size_t g = (size_t)gy * nx + gx;
     const uint32_t cl = (ty + 1) * TL + tx + 1;
     // An edge thread stages at most one row halo cell (north or south) and
-    // one column halo cell (west or east).  The data loads are issued first,
-    // so that they are in flight together with the first hook's shadow load.
+    // one column halo cell (west or east).
     const bool hn = inside && ty == 0 && gy > 0, hs = inside && ty == 15 && gy + 1 < ny;
     const bool hw = inside && tx == 0 && gx > 0, he = inside && tx == 15 && gx + 1 < nx;
     const size_t gr = hn ? g - nx : g + nx, gc = hw ? g - 1 : g + 1;
-    // LDS words of the row and column halo cells, computed where they are used
-    const auto lrow = [&] { return hn ? tx + 1 : 17 * TL + tx + 1; };
-    const auto lcol = [&] { return hw ? (ty + 1) * TL : (ty + 1) * TL + 17; };
-    const uint32_t lr = ONE_HALO ? lrow() : 0u, lc = ONE_HALO ? lcol() : 0u;
-    float vr = 0.0f, vk = 0.0f;
+    const uint32_t lr = hn ? tx + 1 : 17 * TL + tx + 1;
+    const uint32_t lc = hw ? (ty + 1) * TL : (ty + 1) * TL + 17;
+    const hr_el xo = gold.at2(gy, gx, g), xn = gnew.at2(gy, gx, g);
+    // an edge cell is the halo cell of the tile beside it, read there by the
+    // thread next to it
+    const auto by_row = [&] {
+        return hr_by{hn || hs, hn ? lb - nbx : lb + nbx, hn ? 240u + tx : tx, HR_SITE_JACOBI_HALO};
+    };
+    const auto by_col = [&] {
+        return hr_by{hw || he, hw ? lb - 1 : lb + 1, ty * 16u + (hw ? 15u : 0u),
+                     HR_SITE_JACOBI_HALO};
+    };
+    typename G::word qo = 0, qn = 0;
+    // in place (one region as both grids) the new cell's word is the old
+    // cell's, to be loaded after its first update
+    bool in_place = false;
+    if constexpr (CHECK) in_place = gold.shadow == gnew.shadow;
     if (inside) {
         const float vc = uo[g];
-        vr = hn || hs ? uo[gr] : 0.0f;
-        vk = hw || he ? uo[gc] : 0.0f;
-        // Each global hook is settled after the LDS hook of the staging
-        // store that follows it, so the LDS hook runs while the exchange is
-        // in flight.  (The staging hook comes before its store: the store
-        // needs the loaded value, and waiting for it waits for the exchange
-        // too.)
-        // The centre check is blind: it steps from the initial word and
-        // exchanges without loading the word first, and the settle folds
-        // back the word the exchange replaced.  A word of an earlier launch
-        // (or, with 4-byte words, the cleared word) adds nothing to that
-        // fold, and a neighbouring block's halo read of this launch merges
-        // in as another block's access, so the result is the loaded check's;
-        // the wave starts with one round trip instead of two.  (The 4-byte
-        // merge is the 8-byte one on widened words.)
-        const typename G::pend pc = hr_gi<0, CHECK, true>(e, th, gold, gold.at2(gy, gx, g),
-                                                            HR_SITE_JACOBI_CENTRE, 0);
-        hr_l<1, CHECK>(e, th, tsh, TW, lds_id, cl, HR_SITE_JACOBI_STAGE);
+        const float vr = hn || hs ? uo[gr] : 0.0f;
+        const float vk = hw || he ? uo[gc] : 0.0f;
+        if constexpr (CHECK) {
+            qo = hr_gload<CHECK>(th, gold, xo);
+            if (!in_place) qn = hr_gload<CHECK>(th, gnew, xn);
+            // the first access of a tile word this launch: no earlier word
+            const uint32_t staged = hr::l::step(hr::T_INIT, th.lid, hr::CL_X);
+            tsh[cl] = staged;
+            if (hn || hs) tsh[lr] = staged;
+            if (hw || he) tsh[lc] = staged;
+            if (e.count) {
+                hr_note<0, CHECK>(e, th, gold, g, HR_SITE_JACOBI_CENTRE);
+                hr_note_lds<1, CHECK>(e, th, lds_id, cl, HR_SITE_JACOBI_STAGE);
+                if (hn || hs) {
+                    hr_note<0, CHECK>(e, th, gold, gr, HR_SITE_JACOBI_HALO);
+                    hr_note_lds<1, CHECK>(e, th, lds_id, lr, HR_SITE_JACOBI_STAGE);
+                }
+                if (hw || he) {
+                    hr_note<0, CHECK>(e, th, gold, gc, HR_SITE_JACOBI_HALO);
+                    hr_note_lds<1, CHECK>(e, th, lds_id, lc, HR_SITE_JACOBI_STAGE);
+                }
+            }
+        }
         tile[cl] = vc;
-        hr_gs<0, CHECK>(e, th, gold, pc, g, HR_SITE_JACOBI_CENTRE);
-    }
-    if constexpr (!CHECK) {
-        if (hn || hs) tile[ONE_HALO ? lr : lrow()] = vr;
-        if (hw || he) tile[ONE_HALO ? lc : lcol()] = vk;
-    } else if constexpr (!ONE_HALO) {
-        if (hn || hs) {
-            const uint32_t lr = lrow();
-            const typename G::pend pr =
-                hr_gi<0, CHECK>(e, th, gold, gold.at2(hn ? gy - 1 : gy + 1, gx, gr),
-                                HR_SITE_JACOBI_HALO);
-            hr_l<1, CHECK>(e, th, tsh, TW, lds_id, lr, HR_SITE_JACOBI_STAGE);
-            tile[lr] = vr;
-            hr_gs<0, CHECK>(e, th, gold, pr, gr, HR_SITE_JACOBI_HALO);
-        }
-        if (hw || he) {
-            const uint32_t lc = lcol();
-            const typename G::pend pk =
-                hr_gi<0, CHECK>(e, th, gold, gold.at2(gy, hw ? gx - 1 : gx + 1, gc),
-                                HR_SITE_JACOBI_HALO);
-            hr_l<1, CHECK>(e, th, tsh, TW, lds_id, lc, HR_SITE_JACOBI_STAGE);
-            tile[lc] = vk;
-            hr_gs<0, CHECK>(e, th, gold, pk, gc, HR_SITE_JACOBI_HALO);
-        }
-    } else {
-        // The halo reads are checked in one hook section, one check per
-        // lane: a wave's divergent sections run one after another, so a
-        // lane with two halo checks would add a section for the whole
-        // wave.  A lane checks its row halo read, else its column halo read.
-        // The column halo read of a corner lane that also has a row halo is
-        // checked by a proxy lane with no halo of its own: lane (1,1) for
-        // corner (0,0), (1,14) for (0,15), (14,1) for (15,0) and (14,14) for
-        // (15,15).  It is the same access, checked with the corner thread's
-        // identity before the same barrier; the proxy need not own a cell.
-        bool on = hn || hs || hw || he;
-        size_t ha = hn || hs ? gr : gc;
-        uint32_t hy = hn ? gy - 1 : (hs ? gy + 1 : gy);
-        uint32_t hx = hn || hs ? gx : (hw ? gx - 1 : gx + 1);
-        hr_thread hth = th;
-        if (t < 256 && (ty == 1 || ty == 14) && (tx == 1 || tx == 14)) {
-            const uint32_t cy = ty == 1 ? 0u : 15u, cx = tx == 1 ? 0u : 15u;
-            const uint32_t cgx = bx * 16u + cx, cgy = by * 16u + cy;
-            const bool row = (cy == 0 && cgy > 0) || (cy == 15 && cgy + 1 < ny);
-            const bool cw = cx == 0 && cgx > 0, ce = cx == 15 && cgx + 1 < nx;
-            if (cgx < nx && cgy < ny && row && (cw || ce)) {
-                const size_t cg = (size_t)cgy * nx + cgx;
-                on = true;
-                ha = cw ? cg - 1 : cg + 1;
-                hy = cgy;
-                hx = cw ? cgx - 1 : cgx + 1;
-                hth = hr_thread_make(e, lb, cy * 16u + cx);
-            }
-        }
-        if (on) {
-            const typename G::pend ph = hr_gi<0, CHECK>(e, hth, gold, gold.at2(hy, hx, ha),
-                                                                 HR_SITE_JACOBI_HALO);
-            if (hn || hs) {
-                hr_l<1, CHECK>(e, th, tsh, TW, lds_id, lr, HR_SITE_JACOBI_STAGE);
-                tile[lr] = vr;
-            }
-            if (hw || he) {
-                hr_l<1, CHECK>(e, th, tsh, TW, lds_id, lc, HR_SITE_JACOBI_STAGE);
-                tile[lc] = vk;
-            }
-            hr_gs<0, CHECK>(e, hth, gold, ph, ha, HR_SITE_JACOBI_HALO);
-        }
+        if (hn || hs) tile[lr] = vr;
+        if (hw || he) tile[lc] = vk;
+        if constexpr (CHECK)
+            if (!hr_own_fast<0>(e, th, gold, xo, qo, by_row(), by_col())) late |= OLD;
     }
     sync.template bar<CHECK>(e, th);
+    // the centre word is read by its own thread and by the tile's threads
+    // beside it; one of them stands for the others, of another
+    // synchronization group if there is one
+    uint32_t other = HR_NO_THREAD;
+    bool far = false;
+    if constexpr (CHECK) {
+        const uint32_t gm = 1023u >> e.wave_bits << e.wave_bits;
+        const auto reads = [&](bool on, uint32_t u) {
+            const bool f = ((t ^ u) & gm) != 0;
+            if (on && !far) {
+                other = u;
+                far = f;
+            }
+        };
+        reads(tx > 0, t - 1);
+        reads(tx < 15 && gx + 1 < nx, t + 1);
+        reads(ty > 0, t - 16);
+        reads(ty < 15 && gy + 1 < ny, t + 16);
+    }
+    hr_by rows{0, 0, 0, 0}, cols{0, 0, 0, 0};
     if (inside) {
-        // the output word's shadow load is in flight during the LDS reads
-        const hr_el xo = gnew.at2(gy, gx, g);
-        const typename G::word pre_out = hr_gload<CHECK>(th, gnew, xo);
         const float c = tile[cl];
-        hr_l<0, CHECK>(e, th, tsh, TW, lds_id, cl, HR_SITE_JACOBI_TILE);
-        float vn = c, vs = c, vw = c, ve = c;
-        if (gy > 0) {
-            vn = tile[cl - TL];
-            hr_l<0, CHECK>(e, th, tsh, TW, lds_id, cl - TL, HR_SITE_JACOBI_TILE);
-        }
-        if (gy + 1 < ny) {
-            vs = tile[cl + TL];
-            hr_l<0, CHECK>(e, th, tsh, TW, lds_id, cl + TL, HR_SITE_JACOBI_TILE);
-        }
-        if (gx > 0) {
-            vw = tile[cl - 1];
-            hr_l<0, CHECK>(e, th, tsh, TW, lds_id, cl - 1, HR_SITE_JACOBI_TILE);
-        }
-        if (gx + 1 < nx) {
-            ve = tile[cl + 1];
-            hr_l<0, CHECK>(e, th, tsh, TW, lds_id, cl + 1, HR_SITE_JACOBI_TILE);
+        const float vn = gy > 0 ? tile[cl - TL] : c;
+        const float vs = gy + 1 < ny ? tile[cl + TL] : c;
+        const float vw = gx > 0 ? tile[cl - 1] : c;
+        const float ve = gx + 1 < nx ? tile[cl + 1] : c;
+        if constexpr (CHECK) {
+            if (e.count) {
+                hr_note_lds<0, CHECK>(e, th, lds_id, cl, HR_SITE_JACOBI_TILE);
+                if (gy > 0) hr_note_lds<0, CHECK>(e, th, lds_id, cl - TL, HR_SITE_JACOBI_TILE);
+                if (gy + 1 < ny) hr_note_lds<0, CHECK>(e, th, lds_id, cl + TL, HR_SITE_JACOBI_TILE);
+                if (gx > 0) hr_note_lds<0, CHECK>(e, th, lds_id, cl - 1, HR_SITE_JACOBI_TILE);
+                if (gx + 1 < nx) hr_note_lds<0, CHECK>(e, th, lds_id, cl + 1, HR_SITE_JACOBI_TILE);
+            }
+            if (!hr_own_lds_fast<0>(e, th, tsh, cl, other == HR_NO_THREAD ? 0u : far ? 2u : 1u))
+                late |= CENTRE;
+            if ((hn || hs) && !hr_own_lds_fast<0>(e, th, tsh, lr, 0)) late |= ROW;
+            if ((hw || he) && !hr_own_lds_fast<0>(e, th, tsh, lc, 0)) late |= COL;
         }
         const float r = 0.2f * (c + vn + vs + vw + ve);
         un[g] = r;
-        hr_gpre<1, CHECK, false>(e, th, gnew, xo, HR_SITE_JACOBI_OUT, pre_out);
+        if constexpr (CHECK) {
+            if (e.count) hr_note<1, CHECK>(e, th, gnew, g, HR_SITE_JACOBI_OUT);
+        }
         if (seeds) {
             const int32_t sd = seeds[lb];
             if (sd >= 0) {
                 const uint32_t side = (uint32_t)sd >> 8, off = (uint32_t)sd & 255u;
-                uint32_t sy = gy, sx = gx;   // the neighbour-owned target cell
-                bool hit = false;
-                if (side == 0 && ty == 0 && tx == off && gy > 0) hit = true, sy = gy - 1;
-                else if (side == 1 && ty == 15 && tx == off && gy + 1 < ny) hit = true, sy = gy + 1;
-                else if (side == 2 && tx == 0 && ty == off && gx > 0) hit = true, sx = gx - 1;
-                else if (side == 3 && tx == 15 && ty == off && gx + 1 < nx) hit = true, sx = gx + 1;
-                if (hit) {
-                    const size_t tgt = (size_t)sy * nx + sx;
+                size_t tgt = g;              // the neighbour-owned target cell
+                if (side == 0 && ty == 0 && tx == off && gy > 0) tgt = g - nx;
+                else if (side == 1 && ty == 15 && tx == off && gy + 1 < ny) tgt = g + nx;
+                else if (side == 2 && tx == 0 && ty == off && gx > 0) tgt = g - 1;
+                else if (side == 3 && tx == 15 && ty == off && gx + 1 < nx) tgt = g + 1;
+                if (tgt != g) {
                     un[tgt] = r;
-                    hr_g<1, CHECK>(e, th, gnew, gnew.at2(sy, sx, tgt), HR_SITE_JACOBI_SEED);
+                    if constexpr (CHECK) {
+                        if (e.count) hr_note<1, CHECK>(e, th, gnew, tgt, HR_SITE_JACOBI_SEED);
+                    }
                 }
             }
+            if constexpr (CHECK) {
+                // the blocks beside this cell whose seeded write names it
+                const auto names = [&](uint32_t block, uint32_t side, uint32_t off) {
+                    return seeds[block] == (int32_t)(side << 8 | off);
+                };
+                if (hn) rows = hr_by{names(lb - nbx, 1, tx), lb - nbx, 240u + tx, HR_SITE_JACOBI_SEED};
+                if (hs) rows = hr_by{names(lb + nbx, 0, tx), lb + nbx, tx, HR_SITE_JACOBI_SEED};
+                if (hw) cols = hr_by{names(lb - 1, 3, ty), lb - 1, ty * 16u + 15u, HR_SITE_JACOBI_SEED};
+                if (he) cols = hr_by{names(lb + 1, 2, ty), lb + 1, ty * 16u, HR_SITE_JACOBI_SEED};
+            }
         }
+        if constexpr (CHECK)
+            if (in_place || !hr_own_fast<1>(e, th, gnew, xn, qn, rows, cols)) late |= NEW;
+    }
+    if constexpr (CHECK) {
+        if (late == 0) return;
+        if (late & OLD)
+            hr_own<0>(e, hr_thread_of(e, lb, t), gold, xo, HR_SITE_JACOBI_CENTRE, by_row(),
+                      by_col());
+        if (late & CENTRE) hr_own_lds<0>(e, th, tsh, lds_id, cl, HR_SITE_JACOBI_TILE, other);
+        if (late & ROW) hr_own_lds<0>(e, th, tsh, lds_id, lr, HR_SITE_JACOBI_TILE);
+        if (late & COL) hr_own_lds<0>(e, th, tsh, lds_id, lc, HR_SITE_JACOBI_TILE);
+        if (late & NEW) hr_own<1>(e, th, gnew, xn, HR_SITE_JACOBI_OUT, rows, cols);
     }
 }
 
@@ -254,8 +253,9 @@ __global__ __launch_bounds__(256, 8) void k_jacobi(hr_kargs a, hr_gref gold, hr_
     __shared__ float tile[JACOBI_TILE_WORDS];
     __shared__ uint32_t tsh[CHECK ? JACOBI_TILE_WORDS : 1];
     using G = hr_gref_map<0, 0>;
-    jacobi_body<CHECK, G, true>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, gridDim.x, seeds,
-                                blockIdx.y * gridDim.x + blockIdx.x, threadIdx.x, tile, tsh, 0);
+    const uint32_t lb = blockIdx.y * gridDim.x + blockIdx.x;
+    jacobi_body<CHECK, G>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, gridDim.x, seeds,
+                                lb, threadIdx.x, tile, tsh, 0);
 }
 
 // Four consecutive tiles per 1024-thread block, each quarter of the block
@@ -285,16 +285,13 @@ __global__ __launch_bounds__(1024, 8) void k_jacobi_x4(hr_kargs a, hr_gref gold,
         t = UINT32_MAX;
     }
     if constexpr (TILE_SYNC) {
-        if constexpr (CHECK)
-            for (uint32_t i = threadIdx.x; i < 4 * JACOBI_TILE_WORDS; i += 1024)
-                tsh[i / JACOBI_TILE_WORDS][i % JACOBI_TILE_WORDS] = 0;
         if (threadIdx.x < 4) arrive[threadIdx.x] = 0;
         __syncthreads();
-        jacobi_body<CHECK, G, true, hr_tile_sync>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, nbx,
+        jacobi_body<CHECK, G, hr_tile_sync>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, nbx,
                                                   seeds, lb, t, tile[q], tsh[q], 0,
                                                   hr_tile_sync{&arrive[q], 0u});
     } else {
-        jacobi_body<CHECK, G, true>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, nbx, seeds, lb, t,
+        jacobi_body<CHECK, G>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, nbx, seeds, lb, t,
                                     tile[q], tsh[q], 0);
     }
 }
@@ -317,14 +314,13 @@ __global__ __launch_bounds__(256, 8) void k_jacobi_tab(hr_kargs a, hr_gref gold,
     using G = hr_map<hr_gref_tab, 0, 0>;
     const uint16_t* t = tab;
     if constexpr (LDS_TAB) {
-        // the copy is complete before the body's first hook: the body's
-        // first block barrier (after its LDS shadow clear) follows it
         __shared__ uint4 stab[sizeof(hr::g::step_table) / sizeof(uint4)];
         const uint4* src = reinterpret_cast<const uint4*>(tab);
         for (uint32_t i = threadIdx.x; i < sizeof(stab) / sizeof(uint4); i += 256) stab[i] = src[i];
+        __syncthreads();
         t = reinterpret_cast<const uint16_t*>(stab);
     }
-    jacobi_body<CHECK, G, true>(a.env, G{hr_gref_tab{gold, t}}, G{hr_gref_tab{gnew, t}}, uo, un,
+    jacobi_body<CHECK, G>(a.env, G{hr_gref_tab{gold, t}}, G{hr_gref_tab{gnew, t}}, uo, un,
                                 ny, nx, gridDim.x, seeds, blockIdx.y * gridDim.x + blockIdx.x,
                                 threadIdx.x, tile, tsh, 0);
 }
@@ -342,7 +338,7 @@ __global__ __launch_bounds__(256, 8) void k_jacobi_tiled(hr_kargs a, hr_gref gol
     __shared__ float tile[JACOBI_TILE_WORDS];
     __shared__ uint32_t tsh[JACOBI_TILE_WORDS];
     using G = hr_gref_map<TW, TH>;
-    jacobi_body<CHECK, G, true>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, gridDim.x, seeds,
+    jacobi_body<CHECK, G>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, gridDim.x, seeds,
                                blockIdx.y * gridDim.x + blockIdx.x, threadIdx.x, tile, tsh, 0);
 }
 
@@ -359,7 +355,7 @@ __global__ __launch_bounds__(256, LAY ? 8 : 7) void k_jacobi4(hr_kargs a, hr_gre
 {
     __shared__ float tile[JACOBI_TILE_WORDS];
     __shared__ uint32_t tsh[JACOBI_TILE_WORDS];
-    jacobi_body<CHECK, hr_gref4t<LAY>, true>(a.env, gold, gnew, uo, un, ny, nx, gridDim.x, seeds,
+    jacobi_body<CHECK, hr_gref4t<LAY>>(a.env, gold, gnew, uo, un, ny, nx, gridDim.x, seeds,
                                             blockIdx.y * gridDim.x + blockIdx.x, threadIdx.x,
                                             tile, tsh, 0);
 }

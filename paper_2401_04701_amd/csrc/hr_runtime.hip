@@ -193,6 +193,36 @@ void hr_fill_args(hr_ctx c, hr_kargs* a)
     }
 }
 
+// Wait for the exclusive launches of the epoch; from here on it is shared.
+static hr_status epoch_share(hr_ctx c)
+{
+    c->epoch_shared = true;
+    if (!c->epoch_excl) return HR_OK;
+    c->epoch_excl = false;
+    return hipStreamSynchronize(c->epoch_stream) == hipSuccess ? HR_OK : HR_E_HIP;
+}
+
+static void epoch_begin(hr_ctx c)
+{
+    c->epoch_used = c->epoch_shared = c->epoch_excl = false;
+}
+
+hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
+{
+    if (c->epoch_used && c->epoch_stream != s) {
+        const hr_status st = epoch_share(c);
+        if (st != HR_OK) return st;
+    }
+    c->epoch_used = true;
+    c->epoch_stream = s;
+    if (!excl) return HR_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    *excl = !c->epoch_shared && s != hipStreamPerThread &&
+            hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    c->epoch_excl |= *excl != 0;
+    return HR_OK;
+}
+
 bool hr_region_ok(hr_ctx c, uint32_t r, const void* data, size_t min_elems)
 {
     return r < HR_MAX_REGIONS && r < c->reg.size() && c->reg[r].live && c->reg[r].data == data &&
@@ -397,6 +427,8 @@ extern "C" hr_status hr_dev_args(hr_ctx c, void* out, size_t cap, size_t* size_o
     if (!c) return HR_E_INVAL;
     if (size_out) *size_out = sizeof(hr_kargs);
     if (!out || cap < sizeof(hr_kargs)) return HR_E_INVAL;
+    const hr_status st = epoch_share(c);   // the caller's kernel may run on any stream
+    if (st != HR_OK) return st;
     hr_fill_args(c, (hr_kargs*)out);
     return HR_OK;
 }
@@ -448,6 +480,7 @@ extern "C" hr_status hr_kernel_end(hr_ctx c, void* stream)
 {
     if (!c) return HR_E_INVAL;
     c->launch_seq += 1;
+    epoch_begin(c);
     if (c->cfg.flags & HR_CFG_WORD4) {
         // No launch field: every boundary returns the words to INIT.
         hipStream_t s = hr_stream(c, stream);
@@ -490,6 +523,7 @@ extern "C" hr_status hr_reset(hr_ctx c, void* stream)
     if (hr_fill64((uint64_t*)c->count, HR_COUNT_SLOTS, s) != hipSuccess) return HR_E_HIP;
     c->launch_seq = 0;
     c->carried.clear();
+    epoch_begin(c);
     return HR_OK;
 }
 

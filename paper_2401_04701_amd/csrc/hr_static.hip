@@ -96,6 +96,7 @@ extern "C" hr_status hr_job_run_static(const hr_instance* inst, const hr_config*
     // epochs never wrap and the shadow needs no clear in between.
     for (uint32_t p = 0; p < in.phases; ++p) {
         a.env = hr_env_of(k, ring, ctr, count, p);
+        a.env.excl = 1;   // the array is this call's alone, on one stream
         hr_status st;
         switch (in.pattern) {
         case HR_PAT_REDUCE:

@@ -274,6 +274,8 @@ extern "C" hr_status hr_reduce_check(hr_ctx c, uint32_t r_in, uint32_t r_out, co
         return HR_E_INVAL;
     hr_kargs a;
     hr_fill_args(c, &a);
+    const hr_status st = hr_epoch_enter(c, hr_stream(c, stream), nullptr);
+    if (st != HR_OK) return st;
     return hr_launch_reduce(a, r_in, r_out, in_dev, out_dev, n, threads, blocks, drop,
                             hr_stream(c, stream));
 }
@@ -323,6 +325,8 @@ extern "C" hr_status hr_jacobi_check(hr_ctx c, uint32_t r_old, uint32_t r_new,
         return HR_E_INVAL;
     hr_kargs a;
     hr_fill_args(c, &a);
+    const hr_status st = hr_epoch_enter(c, hr_stream(c, stream), &a.env.excl);
+    if (st != HR_OK) return st;
     if (c->cfg.flags & HR_CFG_FSM_TABLE) {
         // the transitions from the flat table: the row-major kernel only
         if (!c->fsm_tab || !u_old_dev || !u_new_dev || !lay_flat(a, r_old) ||
@@ -406,6 +410,8 @@ extern "C" hr_status hr_labelprop_check(hr_ctx c, uint32_t r_label, uint32_t r_r
     if (r_col != UINT32_MAX && !hr_region_ok(c, r_col, col_dev, 1)) return HR_E_INVAL;
     hr_kargs a;
     hr_fill_args(c, &a);
+    const hr_status st = hr_epoch_enter(c, hr_stream(c, stream), nullptr);
+    if (st != HR_OK) return st;
     return hr_launch_labelprop(a, r_label, r_row_ptr, r_col, label_dev, row_ptr_dev, col_dev,
                                mask_dev, n, tpb, hr_stream(c, stream));
 }
@@ -506,6 +512,8 @@ extern "C" hr_status hr_program_check(hr_ctx c, const uint32_t* regions_host, ui
     const size_t lds_bytes = (size_t)lds_words * 2 * sizeof(uint32_t);
     const bool nested = (c->cfg.flags & HR_CFG_NESTED_TILES) != 0;
     if (nested && blocks > hr::n::BLOCK_LIMIT) return HR_E_INVAL;
+    const hr_status st = hr_epoch_enter(c, hr_stream(c, stream), nullptr);
+    if (st != HR_OK) return st;
     if (nested) {
         auto kern = a.env.log ? k_program_nested<true> : k_program_nested<false>;
         HR_LAUNCH(kern, dim3(blocks), dim3(threads), lds_bytes, hr_stream(c, stream), a, pm,
