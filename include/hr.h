@@ -660,7 +660,8 @@ hr_status hr_job_run(const hr_instance* inst, const hr_config* cfg, hr_race* out
  * allocation): the same job, launches and report, but the counters, the
  * report ring (at most HR_STATIC_RING_RECORDS records; a larger
  * cfg->ring_capacity is capped) and the shadow words live in one static
- * device array of HR_STATIC_SCRATCH_BYTES that the library holds on each
+ * device array of HR_STATIC_SCRATCH_BYTES (and 32 KiB of work room behind
+ * them) that the library holds on each
  * device it runs on until the process ends.  The call allocates nothing, on
  * the device or through any allocating library routine; it clears the parts
  * of the array it uses before the first launch, so nothing of an earlier

@@ -32,6 +32,31 @@ __device__ __forceinline__ uint64_t claim(uint32_t* cursor, const uint64_t* item
     return i < n_items ? items[i] : ~0ull;
 }
 
+// Jobs whose pieces' labels are renewed between phases.
+__device__ __forceinline__ bool renews(const hr_inst_dev& I)
+{
+    return I.pattern == HR_PAT_LABELPROP && I.phases > 1;
+}
+
+// The pieces of the run's label-propagation jobs, one wave per entry; first[k]
+// is the number of entries of the jobs before the k-th of them, jobs[k] its
+// place in the job table.
+__global__ __launch_bounds__(256) void k_batch_cut(const hr_inst_dev* __restrict__ insts,
+                                                   const uint32_t* __restrict__ jobs,
+                                                   const uint32_t* __restrict__ first,
+                                                   uint32_t n_jobs)
+{
+    const uint32_t g = uni(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (g >= first[n_jobs]) return;
+    uint32_t lo = 0, hi = n_jobs;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (first[mid] <= g) lo = mid;
+        else hi = mid;
+    }
+    cut_item(load_uniform(insts[jobs[lo]]), g - first[lo]);
+}
+
 // Worker loop.  MIN_WAVES is the occupancy target per SIMD: 4 gives one
 // 1024-thread worker per compute unit with up to 128 registers per lane, 8
 // gives two workers per compute unit within 64 registers (some values then
@@ -61,9 +86,12 @@ __device__ __forceinline__ void batch_loop(const hr_env& base, const hr_inst_dev
         if (threadIdx.x == 0) {
             uint32_t go = 1;
             if (phase > 0) {
+                // (relaxed: an acquire at every poll would invalidate the
+                // caches under the workers that are being waited for)
                 const uint32_t* d = done + I.done_off + phase - 1;
+                const uint32_t all = I.items + (renews(I) ? 1u : 0u);
                 uint32_t spins = 0;
-                while (__hip_atomic_load(d, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < I.items) {
+                while (__hip_atomic_load(d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) {
                     __builtin_amdgcn_s_sleep(8);
                     if (++spins >= spin_limit) {
                         go = 0;
@@ -83,13 +111,33 @@ __device__ __forceinline__ void batch_loop(const hr_env& base, const hr_inst_dev
             run_item(e, I, phase, item, smem);
         }
         __syncthreads();                                // every hook of the item is done
+        uint32_t* const d = done + I.done_off + phase;
         if (threadIdx.x == 0) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            __hip_atomic_fetch_add(done + I.done_off + phase, 1u, __ATOMIC_RELEASE,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+            s_go = __hip_atomic_fetch_add(d, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             s_item = claim(cursor, items, n_items);
         }
         __syncthreads();
+        if (renews(I) && uni(s_go) + 1 == I.items) {
+            // the phase's last item: the labels that the next phase's pieces
+            // continue with (it waits for one count more)
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            for (uint32_t i = threadIdx.x; i <= I.items; i += blockDim.x) {
+                const uint32_t v = I.part[i].v;
+                if (v)
+                    __hip_atomic_store(&I.part[i].label,
+                                       __hip_atomic_load((const int32_t*)I.p0 + (v - 1),
+                                                         __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                __hip_atomic_fetch_add(d, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+        }
     }
 }
 
@@ -196,6 +244,9 @@ struct hr_batch_s {
     uint32_t* d_done = nullptr;
     uint32_t n_done = 0;
     uint32_t* d_cursor = nullptr;
+    lp_part* d_part = nullptr;            // pieces of the label-propagation jobs
+    uint32_t* d_cut = nullptr;            // k_batch_cut's jobs and first
+    uint32_t n_lp = 0, n_part = 0;
     size_t lds_bytes = 0;
     uint32_t max_workers[2] = {0, 0};     // per kernel variant
 };
@@ -209,6 +260,8 @@ extern "C" hr_status hr_batch_destroy(hr_batch b)
         if (p) (void)hipFree(p);
     if (b->d_done) (void)hipFree(b->d_done);
     if (b->d_cursor) (void)hipFree(b->d_cursor);
+    if (b->d_part) (void)hipFree(b->d_part);
+    if (b->d_cut) (void)hipFree(b->d_cut);
     if (b->arena != UINT32_MAX) hr_free_alloc(b->ctx, b->arena);
     delete b;
     return e == hipSuccess ? HR_OK : HR_E_HIP;
@@ -294,6 +347,29 @@ extern "C" hr_status hr_batch_create(hr_ctx c, hr_instance* inst, uint32_t n_ins
         hr_batch_destroy(b);
         return HR_E_INVAL;
     }
+    std::vector<uint32_t> lp_jobs, lp_first(1, 0u);
+    for (uint32_t i = 0; i < n_inst; ++i) {
+        if (inst[i].pattern != HR_PAT_LABELPROP) continue;
+        lp_jobs.push_back(i);
+        lp_first.push_back(lp_first.back() + hd[i].items + 1);
+    }
+    b->n_lp = (uint32_t)lp_jobs.size();
+    b->n_part = lp_first.back();
+    if (b->n_lp) {
+        std::vector<uint32_t> cut(lp_jobs);
+        cut.insert(cut.end(), lp_first.begin(), lp_first.end());
+        if (hipMalloc(&b->d_part, sizeof(lp_part) * b->n_part) != hipSuccess ||
+            hipMalloc(&b->d_cut, sizeof(uint32_t) * cut.size()) != hipSuccess) {
+            hr_batch_destroy(b);
+            return HR_E_NOMEM;
+        }
+        if (hipMemcpy(b->d_cut, cut.data(), sizeof(uint32_t) * cut.size(),
+                      hipMemcpyHostToDevice) != hipSuccess) {
+            hr_batch_destroy(b);
+            return HR_E_HIP;
+        }
+        for (uint32_t k = 0; k < b->n_lp; ++k) hd[lp_jobs[k]].part = b->d_part + lp_first[k];
+    }
     if (hipMalloc(&b->d_inst, sizeof(hr_inst_dev) * n_inst) != hipSuccess ||
         hipMalloc(&b->d_items[0], sizeof(uint64_t) * q[0].size()) != hipSuccess ||
         hipMalloc(&b->d_items[1], sizeof(uint64_t) * q[1].size()) != hipSuccess ||
@@ -377,6 +453,9 @@ extern "C" hr_status hr_batch_run(hr_batch b, const hr_batch_tuning* tune, void*
         hr_fill32(b->d_done, b->n_done, s) != hipSuccess ||
         hr_fill32(b->d_cursor, 1, s) != hipSuccess)
         return HR_E_HIP;
+    if (b->n_lp)
+        HR_LAUNCH(k_batch_cut, dim3((b->n_part + 3) / 4), dim3(256), 0, s, b->d_inst, b->d_cut,
+                  b->d_cut + b->n_lp, b->n_lp);
     hr_env e = hr_make_env(c);
     e.excl = 1;         // the arena is this run's, and a job's phases are ordered
     e.site_limit = 0;   // site ids are per job; the limit does not apply to a batch

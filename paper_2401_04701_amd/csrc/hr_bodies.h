@@ -91,104 +91,222 @@ __device__ void reduce_body(const hr_env& e, const G& gin, const G& gout,
 // of label[u].  grp / gcol: optional monitoring of the CSR reads (shadow null
 // when off).  Two physical forms of the same accesses; this one:
 //
-// The hardware block takes the nv consecutive vertices v0 .. v0+nv, loads
-// their labels and row pointers (one lane per vertex), and after a block
-// barrier all its lanes walk the vertices' edges, which are consecutive in
-// CSR, whichever vertex they belong to.  An edge is checked with the identity
-// of its vertex's logical thread (block and thread index, found by a search
-// of the row pointers in LDS), so the accesses and their happens-before are
-// the program's; the hardware barrier is no barrier of the program.  A
-// logical thread's edges then run side by side on several lanes: the job has
-// no barrier, so all its accesses lie in one epoch, where the order of one
-// thread's updates does not change a summary (step and merge take them as one
-// thread's).  An atomic min that would not lower the label is only its atomic
-// load (the same access class and the same value): the hubs' labels are hot,
-// and memory-side atomics on one line run one after another.
+// A hardware block takes consecutive vertices and consecutive edges, loads
+// the vertices' labels and row pointers (one lane per vertex), and after a
+// block barrier all its lanes walk the edges, whichever vertex they belong
+// to.  An edge is checked with the identity of its vertex's logical thread
+// (block and thread index, found by a search of the row pointers in LDS), so
+// the accesses and their happens-before are the program's; the hardware
+// barrier is no barrier of the program.  A logical thread's edges then run
+// side by side on several lanes: the job has no barrier, so all its accesses
+// lie in one epoch, where the order of one thread's updates does not change a
+// summary (step and merge take them as one thread's).  An atomic min that
+// would not lower the label is only its atomic load (the same access class
+// and the same value): the hubs' labels are hot, and memory-side atomics on
+// one line run one after another.
 //
+// The blocks' shares are equal (lp_part): vertices and edges are put in one
+// order, each vertex before its edges, and cut into pieces of one length, so
+// a hub's edges spread over several blocks.  Its thread loads its label once,
+// so those blocks take the value that was read where the pieces were cut.
+// Cut by vertices instead, the block of the largest hubs bounded every
+// launch: on R-MAT graphs of 50 K to 250 K vertices it holds 80 K to 180 K
+// edges, 6 us a round of 1024.
+
+// Where piece i of a job begins: its first vertex v, its first edge
+// i * length - v, and, when that edge belongs to vertex v - 1, that vertex's
+// label.
+struct lp_part {
+    uint32_t v;
+    int32_t label;
+};
+
+// Length of a piece when n vertices and row_ptr[n] edges are cut into
+// `pieces`, and the first position of piece i.
+__device__ __forceinline__ uint64_t lp_edges(const int32_t* __restrict__ rp, uint32_t n)
+{
+    return (uint64_t)max(rp[n], 0);
+}
+__device__ __forceinline__ uint64_t lp_begin(uint64_t edges, uint32_t n, uint32_t pieces,
+                                             uint32_t i)
+{
+    const uint64_t total = edges + n, len = (total + pieces - 1) / pieces;
+    return min(total, len * i);
+}
+
+// Find the begin of piece i (i <= pieces), one wave.  Vertex v lies at
+// position v + row_ptr[v]: the piece's first vertex is the first one at or
+// past the piece's begin, found by 64 probes a round.
+__device__ __forceinline__ void lp_cut(lp_part* __restrict__ part, const int32_t* label,
+                                       const int32_t* __restrict__ rp, uint32_t n,
+                                       uint32_t pieces, uint32_t i)
+{
+    const uint32_t lane = __lane_id();
+    const uint64_t at = lp_begin(lp_edges(rp, n), n, pieces, i);
+    uint32_t lo = 0, hi = n;               // the answer is in lo..hi
+    while (lo < hi) {
+        const uint32_t m = hi - lo, step = (m + 63u) / 64u;
+        const uint64_t q = (uint64_t)lo + (uint64_t)lane * step + step - 1;
+        const uint64_t hit = __ballot(q < hi && q + (uint64_t)max(rp[q < hi ? q : lo], 0) >= at);
+        if (hit == 0) {
+            lo += m / step * step;
+        } else {
+            const uint32_t f = (uint32_t)__builtin_ctzll(hit);
+            lo += f * step;
+            hi = lo + step - 1;
+        }
+    }
+    if (lane == 0) {
+        const bool cont = lo > 0 && at - lo < (uint64_t)max(rp[lo], 0);
+        part[i].v = lo;
+        part[i].label = cont ? __hip_atomic_load(label + (lo - 1), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT)
+                             : 0;
+    }
+}
+
+// Vertices and edges of a hardware block.  Without pieces (cut false) the
+// edges are those of its vertices.
+struct lp_share {
+    uint32_t v0, v1;
+    bool cut;
+    uint32_t e0, e1;         // cut: the edges
+    int32_t l0;              // cut: label of v0 - 1, for edges below row_ptr[v0]
+    int32_t l1;              // label of v1 - 1 when its edges go on in the
+    bool cont;               // next piece (cont)
+    bool pilot;              // one wave's edges first (labelprop_edges)
+};
+
+__device__ __forceinline__ lp_share lp_share_of(const lp_part* part, const int32_t* __restrict__ rp,
+                                                uint32_t n, uint32_t pieces, uint32_t i)
+{
+    const uint64_t edges = lp_edges(rp, n);
+    const auto load = [&](uint32_t k) {   // the batch's workers renew the labels
+        const uint64_t w = __hip_atomic_load(reinterpret_cast<const uint64_t*>(part + k),
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return lp_part{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)w),
+                       __builtin_amdgcn_readfirstlane((int)(w >> 32))};
+    };
+    const lp_part p0 = load(i), p1 = load(i + 1);
+    lp_share s;
+    s.v0 = p0.v;
+    s.v1 = max(p1.v, p0.v);
+    s.cut = true;
+    s.e0 = (uint32_t)min(edges, lp_begin(edges, n, pieces, i) - p0.v);
+    s.e1 = (uint32_t)min(edges, lp_begin(edges, n, pieces, i + 1) - p1.v);
+    s.l0 = p0.label;
+    s.l1 = p1.label;
+    s.cont = (int32_t)s.e1 < rp[s.v1];
+    return s;
+}
+
 // What bounds it: random requests past the L2, a label and a shadow word per
-// edge (about 22 G requests/s here), and for small graphs the block that
-// holds the largest hub.  R-MAT of 2^22 vertices and 2^25 edges: 3.0 ms per
-// checked launch against 45.7 ms with one lane per vertex (a hub's lane walks
-// tens of thousands of edges, a round trip each), and 7.0 ms with every
-// atomic min performed.  One edge per lane at a time, in 64 registers (two
-// 1024-thread blocks per compute unit), was as fast as 2 or 4 edges per lane
-// (3.2 and 3.3 ms, with more registers) and as loading the next edge's words
-// ahead (3.0 ms, the small graph slower).
+// edge, and in smaller graphs the hubs' words: until the first update of a
+// hub's word lands, every lane with an edge into the hub exchanges the word,
+// and exchanges of one word run one after another.  So in the blocks that
+// start the launch (sh.pilot) one wave's edges go first, and the others find
+// the hubs' words settled.  Per checked launch, R-MAT: 100,003 vertices and
+// 800,024 edges, CSR monitored, 0.070 ms (0.16 without the first wave's
+// start, 0.26 cut by vertices); 2^22 vertices and 2^25 edges 0.73 ms (3.2 cut
+// by vertices).  One edge per lane at a time, in 64
+// registers (two 1024-thread blocks per compute unit), was as fast as 2 or 4
+// edges per lane (with more registers) and as loading the next edge's words
+// ahead.  vt: vertices loaded at a time.
 template <int CHECK, class G>
 __device__ __forceinline__ void labelprop_edges(const hr_env& e, const G& glab, const G& grp,
                                                 const G& gcol, int32_t* __restrict__ label,
                                                 const int32_t* __restrict__ rp,
                                                 const int32_t* __restrict__ col,
                                                 const uint8_t* __restrict__ mask, uint32_t n,
-                                                uint32_t T, uint32_t v0, uint32_t nv, uint32_t* lds)
+                                                uint32_t T, const lp_share& sh, uint32_t vt,
+                                                uint32_t* lds)
 {
-    int32_t* s_rp = (int32_t*)lds;               // nv + 1 row pointers
-    int32_t* s_l = s_rp + nv + 1;                // labels
-    uint32_t* s_id = (uint32_t*)(s_l + nv);      // logical block << 10 | thread
-    for (uint32_t i = threadIdx.x; i < nv; i += blockDim.x) {
-        const uint32_t v = v0 + i, lb = v / T, t = v - lb * T;
-        hr_thread th{};
-        if constexpr (CHECK) {
-            th = hr_thread_make(e, lb, t);
-            s_id[i] = lb << 10 | t;
+    uint32_t* s_rp = lds;                        // row pointers of v0 - 1 (where its
+    int32_t* s_l = (int32_t*)(s_rp + vt + 2);    // edges begin here), the vertices, the end;
+    uint32_t* s_id = (uint32_t*)(s_l + vt + 1);  // labels; logical block << 10 | thread
+    for (uint32_t tv = sh.v0;;) {
+        const uint32_t nv = min(vt, sh.v1 - tv);
+        const bool head = tv == sh.v0, tail = tv + nv == sh.v1;
+        if (threadIdx.x == 0) {
+            s_rp[0] = sh.cut && head ? sh.e0 : (uint32_t)rp[tv];
+            s_l[0] = sh.l0;
+            s_id[0] = tv == 0 ? 0u : (tv - 1) / T << 10 | (tv - 1) % T;
         }
-        const typename G::word q = hr_gload<CHECK>(th, glab, v);
-        const int32_t l = __hip_atomic_load(label + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int32_t r = rp[v];
-        if (i + 1 == nv) s_rp[nv] = rp[v + 1];
-        const typename G::pend p = hr_gi<2, CHECK, true>(e, th, glab, v, HR_SITE_LP_OWN, q);
-        s_l[i] = l;
-        s_rp[i] = r;
-        hr_gs<2, CHECK>(e, th, glab, p, v, HR_SITE_LP_OWN);
-        if (CHECK && grp.shadow) {
-            hr_g<0, CHECK>(e, th, grp, v, HR_SITE_LP_CSR);
-            hr_g<0, CHECK>(e, th, grp, v + 1, HR_SITE_LP_CSR);
+        for (uint32_t i = threadIdx.x; i < nv; i += blockDim.x) {
+            const uint32_t v = tv + i, lb = v / T, t = v - lb * T;
+            hr_thread th{};
+            if constexpr (CHECK) {
+                th = hr_thread_make(e, lb, t);
+                s_id[i + 1] = lb << 10 | t;
+            }
+            const typename G::word q = hr_gload<CHECK>(th, glab, v);
+            int32_t l = __hip_atomic_load(label + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (sh.cut && sh.cont && v + 1 == sh.v1) l = sh.l1;
+            const uint32_t r = (uint32_t)rp[v];
+            if (i + 1 == nv) s_rp[nv + 1] = (uint32_t)rp[v + 1];
+            const typename G::pend p = hr_gi<2, CHECK, true>(e, th, glab, v, HR_SITE_LP_OWN, q);
+            s_l[i + 1] = l;
+            s_rp[i + 1] = r;
+            hr_gs<2, CHECK>(e, th, glab, p, v, HR_SITE_LP_OWN);
+            if (CHECK && grp.shadow) {
+                hr_g<0, CHECK>(e, th, grp, v, HR_SITE_LP_CSR);
+                hr_g<0, CHECK>(e, th, grp, v + 1, HR_SITE_LP_CSR);
+            }
         }
-    }
-    __syncthreads();
-    const int64_t e1 = s_rp[nv];
-    for (int64_t k = (int64_t)s_rp[0] + threadIdx.x; k < e1; k += blockDim.x) {
-        const uint32_t u = (uint32_t)col[k];
-        const bool seeded = mask[k];
-        typename G::word w = 0;
-        if constexpr (CHECK) w = hr_gload<CHECK>(hr_thread_of(e, 0, 0), gcol, (uint64_t)k);
-        // the edge's vertex: the last i with s_rp[i] <= k
-        uint32_t lo = 0, hi = nv;
-        while (hi - lo > 1) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (s_rp[mid] <= k) lo = mid;
-            else hi = mid;
+        __syncthreads();
+        const uint32_t k0 = sh.cut && head ? sh.e0 : s_rp[1];
+        const uint32_t k1 = sh.cut && tail ? sh.e1 : s_rp[nv + 1];
+        const uint32_t rounds = k1 > k0 ? (k1 - k0 + blockDim.x - 1) / blockDim.x : 0;
+        const bool pilot = sh.pilot && head;
+        for (uint32_t j = pilot ? 0 : 1; j <= rounds; ++j) {       // uniform
+            if (pilot && j == 1) __syncthreads();
+            const uint32_t k = k0 + threadIdx.x + (j ? j - 1 : 0) * blockDim.x;
+            if (k >= k1 || (pilot && j < 2 && (threadIdx.x < 64) != (j == 0))) continue;
+            const uint32_t u = (uint32_t)col[k];
+            const bool seeded = mask[k];
+            typename G::word w = 0;
+            if constexpr (CHECK) w = hr_gload<CHECK>(hr_thread_of(e, 0, 0), gcol, (uint64_t)k);
+            // the edge's vertex: the last one whose edges begin at or before k
+            uint32_t lo = 0, hi = nv + 1;
+            while (hi - lo > 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if (s_rp[mid] <= k) lo = mid;
+                else hi = mid;
+            }
+            const int32_t l = s_l[lo];
+            hr_thread th{};
+            if constexpr (CHECK) th = hr_thread_of(e, s_id[lo] >> 10, s_id[lo] & 1023u);
+            typename G::word q = 0;
+            typename G::pend pu{}, pc{};
+            int32_t cur = 0;
+            if (u < n) {
+                q = hr_gload<CHECK>(th, glab, u);
+                cur = __hip_atomic_load(label + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (CHECK && gcol.shadow)
+                pc = hr_gi<0, CHECK, true>(e, th, gcol, (uint64_t)k, HR_SITE_LP_CSR, w);
+            if (u < n && !seeded) {
+                if (cur > l) atomicMin(label + u, l);
+                pu = hr_gi<2, CHECK, true>(e, th, glab, u, HR_SITE_LP_MIN, q);
+            }
+            if (CHECK && gcol.shadow)
+                hr_gs<0, CHECK>(e, th, gcol, pc, (uint64_t)k, HR_SITE_LP_CSR);
+            hr_gs<2, CHECK>(e, th, glab, pu, u, HR_SITE_LP_MIN);
+            if (u < n && seeded) {
+                const int32_t r = label[u];
+                hr_gpre<0, CHECK, false>(e, th, glab, u, HR_SITE_LP_SEED_READ, q);
+                label[u] = r < l ? r : l;
+                hr_g<1, CHECK>(e, th, glab, u, HR_SITE_LP_SEED_WRITE);
+            }
         }
-        const int32_t l = s_l[lo];
-        hr_thread th{};
-        if constexpr (CHECK) th = hr_thread_of(e, s_id[lo] >> 10, s_id[lo] & 1023u);
-        typename G::word q = 0;
-        typename G::pend pu{}, pc{};
-        int32_t cur = 0;
-        if (u < n) {
-            q = hr_gload<CHECK>(th, glab, u);
-            cur = __hip_atomic_load(label + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (CHECK && gcol.shadow)
-            pc = hr_gi<0, CHECK, true>(e, th, gcol, (uint64_t)k, HR_SITE_LP_CSR, w);
-        if (u < n && !seeded) {
-            if (cur > l) atomicMin(label + u, l);
-            pu = hr_gi<2, CHECK, true>(e, th, glab, u, HR_SITE_LP_MIN, q);
-        }
-        if (CHECK && gcol.shadow)
-            hr_gs<0, CHECK>(e, th, gcol, pc, (uint64_t)k, HR_SITE_LP_CSR);
-        hr_gs<2, CHECK>(e, th, glab, pu, u, HR_SITE_LP_MIN);
-        if (u < n && seeded) {
-            const int32_t r = label[u];
-            hr_gpre<0, CHECK, false>(e, th, glab, u, HR_SITE_LP_SEED_READ, q);
-            label[u] = r < l ? r : l;
-            hr_g<1, CHECK>(e, th, glab, u, HR_SITE_LP_SEED_WRITE);
-        }
+        tv += nv;
+        if (tv >= sh.v1) return;
+        __syncthreads();
     }
 }
 
-// LDS words labelprop_edges needs for nv vertices.
-constexpr uint32_t labelprop_lds_words(uint32_t nv) { return 3 * nv + 1; }
+// LDS words labelprop_edges needs for vt vertices at a time.
+constexpr uint32_t labelprop_lds_words(uint32_t vt) { return 3 * vt + 4; }
 
 // The other form: one lane per logical thread, vertices lb*T .. lb*T+T, one
 // edge at a time.  For contexts with wave grouping, whose hook instructions

@@ -21,6 +21,7 @@ struct hr_inst_dev {
     uint32_t done_off, lds_id;
     uint32_t pack, items;     // logical blocks per work item; work items per phase
     uint32_t lds_words;       // LDS words of one logical block
+    lp_part* part;            // label propagation: where the items' pieces begin (items + 1)
     hr_gref g0, g1;
     const void* p0;
     void* p1;
@@ -103,14 +104,22 @@ __device__ __forceinline__ void run_item(const hr_env& e, const hr_inst_dev& I, 
                 labelprop_body<1>(e, G{I.g0}, none, none, (int32_t*)I.p0, (const int32_t*)I.p1,
                                   (const int32_t*)I.p2, (const uint8_t*)I.p3, I.n, T, lb, t);
             } else {
-                const uint32_t vb = I.pack * T, v0 = item * vb;
-                labelprop_edges<1>(
-                    e, G{I.g0}, none, none, (int32_t*)I.p0, (const int32_t*)I.p1,
-                    (const int32_t*)I.p2, (const uint8_t*)I.p3, I.n, T, v0, min(vb, I.n - v0),
-                    smem);
+                lp_share sh = lp_share_of(I.part, (const int32_t*)I.p1, I.n, I.items, item);
+                // about the items that start a phase (a batch of 56 mixed jobs
+                // 7.3 ms without, 6.7 with)
+                sh.pilot = item < 512;
+                labelprop_edges<1>(e, G{I.g0}, none, none, (int32_t*)I.p0, (const int32_t*)I.p1,
+                                   (const int32_t*)I.p2, (const uint8_t*)I.p3, I.n, T, sh,
+                                   HR_WORKER_THREADS, smem);
             }
         }
     }
+}
+
+// Entry i of the pieces of a label-propagation job, one wave.
+__device__ __forceinline__ void cut_item(const hr_inst_dev& I, uint32_t i)
+{
+    lp_cut(I.part, (const int32_t*)I.p0, (const int32_t*)I.p1, I.n, I.items, i);
 }
 
 // The descriptor as every thread of the worker block sees it, in scalar
@@ -131,6 +140,7 @@ __device__ __forceinline__ hr_inst_dev load_uniform(const hr_inst_dev& G)
     I.pack = uni(G.pack);
     I.items = uni(G.items);
     I.lds_words = uni(G.lds_words);
+    I.part = unip(G.part);
     I.g0 = uni_gref(G.g0);
     I.g1 = uni_gref(G.g1);
     I.p0 = unip(G.p0);

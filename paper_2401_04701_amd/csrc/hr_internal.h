@@ -8,6 +8,11 @@
 #include "hr.h"
 #include "hr_device.h"
 
+struct lp_part;   // hr_bodies.h
+
+// Most pieces of a label-propagation launch (8 rounds of resident blocks).
+constexpr uint32_t HR_LP_PIECES = 4096;
+
 static_assert(sizeof(hr_race) == sizeof(hr_race_rec), "hr_race layout");
 static_assert(sizeof(hr_access_rec) == 32, "hr_access_rec layout");
 
@@ -51,6 +56,10 @@ struct hr_ctx_s {
     // env.excl.
     bool epoch_used = false, epoch_shared = false, epoch_excl = false;
     hipStream_t epoch_stream = nullptr;
+    // Room for the pieces of a label-propagation launch (after the debug
+    // counters, in their allocation) and the stream that used it last.
+    bool lp_used = false;
+    hipStream_t lp_stream = nullptr;
 };
 
 // Account for a checked launch on `s` in the current launch epoch.  *excl
@@ -77,6 +86,12 @@ hr_env hr_env_of(const hr_config& cfg, hr_race_rec* ring, uint32_t* ctr,
                  unsigned long long* count, uint32_t launch_seq, hr_access_rec* log = nullptr);
 hr_env hr_make_env(hr_ctx c);
 void hr_fill_args(hr_ctx c, hr_kargs* a);
+// The context's room for the pieces of a label-propagation launch on `s`, or
+// NULL: a launch on another stream may still use it, or `s` is being captured
+// or names several streams (see hr_epoch_enter).
+lp_part* hr_lp_room(hr_ctx c, hipStream_t s);
+// Bytes of that room.
+constexpr size_t HR_LP_ROOM_BYTES = (HR_LP_PIECES + 1) * 8;
 // A region usable through kernel arguments (id < HR_MAX_REGIONS), registered
 // for `data` and holding at least min_elems elements.
 bool hr_region_ok(hr_ctx c, uint32_t r, const void* data, size_t min_elems);
@@ -117,7 +132,7 @@ hr_status hr_launch_jacobi(const hr_kargs& a, uint32_t r_old, uint32_t r_new,
 hr_status hr_launch_labelprop(const hr_kargs& a, uint32_t r_label, uint32_t r_row_ptr,
                               uint32_t r_col, int32_t* label_dev, const int32_t* row_ptr_dev,
                               const int32_t* col_dev, const uint8_t* mask_dev, uint32_t n,
-                              uint32_t tpb, hipStream_t s);
+                              uint32_t tpb, lp_part* part, hipStream_t s);
 
 #define HR_HIP_CHECK(expr)                              \
     do {                                                \

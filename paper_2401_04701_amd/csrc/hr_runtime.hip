@@ -207,6 +207,14 @@ static void epoch_begin(hr_ctx c)
     c->epoch_used = c->epoch_shared = c->epoch_excl = false;
 }
 
+// A handle of one stream, whose launches run now and not as a graph's.
+static bool one_eager_stream(hipStream_t s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return s != hipStreamPerThread && hipStreamIsCapturing(s, &cap) == hipSuccess &&
+           cap == hipStreamCaptureStatusNone;
+}
+
 hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
 {
     if (c->epoch_used && c->epoch_stream != s) {
@@ -216,11 +224,21 @@ hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
     c->epoch_used = true;
     c->epoch_stream = s;
     if (!excl) return HR_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    *excl = !c->epoch_shared && s != hipStreamPerThread &&
-            hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    *excl = !c->epoch_shared && one_eager_stream(s);
     c->epoch_excl |= *excl != 0;
     return HR_OK;
+}
+
+lp_part* hr_lp_room(hr_ctx c, hipStream_t s)
+{
+    if (!one_eager_stream(s)) return nullptr;
+    if (c->lp_used && c->lp_stream != s && hipStreamQuery(c->lp_stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    c->lp_used = true;
+    c->lp_stream = s;
+    return (lp_part*)(c->count + HR_COUNT_SLOTS);
 }
 
 bool hr_region_ok(hr_ctx c, uint32_t r, const void* data, size_t min_elems)
@@ -339,7 +357,8 @@ extern "C" hr_status hr_ctx_create(hr_ctx* out, const hr_config* cfg, void* stre
         return HR_E_NOMEM;
     }
     c->ring = (hr_race_rec*)((uint8_t*)c->ctr + HR_CTR_BYTES);
-    if (hipMalloc(&c->count, sizeof(unsigned long long) * HR_COUNT_SLOTS) != hipSuccess ||
+    if (hipMalloc(&c->count, sizeof(unsigned long long) * HR_COUNT_SLOTS + HR_LP_ROOM_BYTES) !=
+            hipSuccess ||
         ((k.flags & HR_CFG_ACCESS_LOG) &&
          hipMalloc(&c->log, sizeof(hr_access_rec) * (size_t)k.log_capacity) != hipSuccess) ||
         ((k.flags & HR_CFG_FSM_TABLE) && hipMalloc(&c->fsm_tab, sizeof(FSM_TABLE)) != hipSuccess)) {

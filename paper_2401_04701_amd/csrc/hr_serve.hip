@@ -57,6 +57,24 @@ __global__ __launch_bounds__(1024, 8) void k_iter(hr_env base, const hr_inst_dev
     run_item<PATTERNS>(e, I, phase, item, smem);
 }
 
+// The pieces of the resident jobs of a label-propagation iteration, one wave
+// per entry: job k's entries are prefix[k] + k up to prefix[k+1] + k.
+__global__ __launch_bounds__(256) void k_iter_cut(const hr_inst_dev* __restrict__ slots,
+                                                  const uint32_t* __restrict__ act,
+                                                  const uint64_t* __restrict__ prefix,
+                                                  uint32_t n_act)
+{
+    const uint32_t g = uni(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (g >= uni64(prefix[n_act]) + n_act) return;
+    uint32_t lo = 0, hi = n_act;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (uni64(prefix[mid]) + mid <= g) lo = mid;
+        else hi = mid;
+    }
+    cut_item(load_uniform(slots[uni(act[lo]) & 0xFFFFFu]), g - (uint32_t)uni64(prefix[lo]) - lo);
+}
+
 // One phase of a stencil job of the large lane: the stencil's tuned body,
 // four tiles to a 1024-thread block (k_jacobi_x4), on the job's shadow
 // words in the arena, under the lane's environment with the phase's launch
@@ -98,6 +116,7 @@ struct job_state {
     size_t elems[2] = {0, 0};
     uint64_t off = 0, granules = 0;   // arena placement
     uint32_t items = 0;               // work items of one phase
+    uint64_t part = 0;                // its first entry in serve_buffers::part
     uint32_t slot = 0, phase = 0;
     uint32_t burst = 1;               // phases its lane's iteration in flight runs
     int32_t status = 0;
@@ -209,6 +228,7 @@ struct serve_buffers {
     uint64_t* arena = nullptr;
     hr_inst_dev* slots = nullptr;
     hr_inst_dev* h_desc = nullptr;   // pinned staging
+    lp_part* part = nullptr;         // pieces of the label-propagation jobs
     lane_state lane[N_LANES];
     ~serve_buffers()
     {
@@ -229,6 +249,7 @@ struct serve_buffers {
         }
         if (arena) (void)hipFree(arena);
         if (slots) (void)hipFree(slots);
+        if (part) (void)hipFree(part);
         if (h_desc) (void)hipHostFree(h_desc);
     }
 };
@@ -269,7 +290,7 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
     std::vector<uint32_t> lane_of_job(n);
     size_t lds[N_LANES] = {};
     const uint64_t budget_granules = cfg.shadow_budget / (GRANULE_WORDS * 8);
-    uint64_t need = 0;
+    uint64_t need = 0, n_part = 0;
     for (uint32_t j = 0; j < n; ++j) {
         js[j].in = jobs[j];
         size_t l = 0;
@@ -282,6 +303,8 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
         lane_of_job[j] = lane_of(js[j].in, js[j].items);
         lds[lane_of_job[j]] = std::max(lds[lane_of_job[j]], l);
         need += js[j].granules;
+        js[j].part = n_part;
+        if (js[j].in.pattern == HR_PAT_LABELPROP) n_part += js[j].items + 1;
     }
     // the arena never needs more than every job at once
     const uint64_t arena_granules = std::min(budget_granules, need);
@@ -292,6 +315,7 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
         hipHostMalloc(&b.h_desc, sizeof(hr_inst_dev) * max_slots, hipHostMallocDefault) !=
             hipSuccess)
         return HR_E_NOMEM;
+    if (n_part && hipMalloc(&b.part, sizeof(lp_part) * n_part) != hipSuccess) return HR_E_NOMEM;
     hr_env env[N_LANES];
     const hr_env env_base = hr_make_env(c);
     for (uint32_t k = 0; k < N_LANES; ++k) {
@@ -341,6 +365,7 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
             uint64_t* sh1 = st.elems[1] ? sh0 + st.elems[0] : nullptr;
             if (hr_fill64(sh0, st.elems[0] + st.elems[1], L.s) != hipSuccess) return HR_E_HIP;
             b.h_desc[st.slot] = hr_make_inst_dev(st.in, st.elems, sh0, sh1, 2 * next, 2 * next + 1, 0);
+            if (st.in.pattern == HR_PAT_LABELPROP) b.h_desc[st.slot].part = b.part + st.part;
             if (hipMemcpyAsync(b.slots + st.slot, b.h_desc + st.slot, sizeof(hr_inst_dev),
                                hipMemcpyHostToDevice, L.s) != hipSuccess)
                 return HR_E_HIP;
@@ -395,6 +420,9 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
                         hipMemcpyAsync(d_pre, pre, sizeof(uint64_t) * (m + 1),
                                        hipMemcpyHostToDevice, L.s) != hipSuccess)
                         return HR_E_HIP;
+                    if (patterns & (1u << HR_PAT_LABELPROP))
+                        HR_LAUNCH(k_iter_cut, dim3((uint32_t)((total + m + 3) / 4)), dim3(256), 0,
+                                  L.s, b.slots, d_act, d_pre, m);
                     HR_LAUNCH(iter_for(patterns), dim3((uint32_t)total), dim3(HR_WORKER_THREADS),
                               L.lds, L.s, env[k], b.slots, d_act, d_pre, m);
                     ++iters;

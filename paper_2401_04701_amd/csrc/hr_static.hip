@@ -30,8 +30,12 @@ static_assert(OFF_SHADOW % 256 == 0, "shadow words start on a 256-byte boundary"
 static_assert(OFF_SHADOW + (size_t)HR_STATIC_SHADOW_WORDS * 8 <= HR_STATIC_SCRATCH_BYTES,
               "shadow words fit");
 
+// Behind the documented scratch bytes: room for the pieces of a
+// label-propagation launch.
+constexpr size_t OFF_PIECES = HR_STATIC_SCRATCH_BYTES;
+
 // The scratch memory: one copy per device, resident while the process lives.
-static __device__ __align__(256) uint64_t scratch[HR_STATIC_SCRATCH_BYTES / 8];
+static __device__ __align__(256) uint64_t scratch[(OFF_PIECES + HR_LP_ROOM_BYTES) / 8];
 
 constexpr int MAX_DEVICES = 64;
 std::mutex g_lock;                    // serialises calls of this process
@@ -114,7 +118,8 @@ extern "C" hr_status hr_job_run_static(const hr_instance* inst, const hr_config*
             st = hr_launch_labelprop(a, 0, UINT32_MAX, UINT32_MAX,
                                      (int32_t*)const_cast<void*>(in.data[0]),
                                      (const int32_t*)in.data[1], (const int32_t*)in.data[2],
-                                     (const uint8_t*)in.data[3], in.n, in.threads, s);
+                                     (const uint8_t*)in.data[3], in.n, in.threads,
+                                     (lp_part*)(base + OFF_PIECES), s);
             break;
         }
         if (st != HR_OK) return st;

@@ -78,20 +78,40 @@ __global__ __launch_bounds__(1024) void k_labelprop(hr_kargs a, R glab, R grp, R
                           blockIdx.x, threadIdx.x);
 }
 
-// Blocks of consecutive vertices whose edges all lanes walk (labelprop_edges);
-// tpb: threads per logical block, vb: vertices per hardware block.
+// Where each of the `pieces` begins, one wave per piece and one for the end.
+__global__ __launch_bounds__(256) void k_labelprop_cut(lp_part* __restrict__ part,
+                                                       const int32_t* label,
+                                                       const int32_t* __restrict__ rp, uint32_t n,
+                                                       uint32_t pieces)
+{
+    const uint32_t i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i <= pieces) lp_cut(part, label, rp, n, pieces, i);
+}
+
+// Blocks whose lanes all walk its edges (labelprop_edges): piece blockIdx.x
+// of part, or without it vb consecutive vertices; tpb: threads per logical
+// block.
 template <int CHECK, class R, class G>
 __global__ __launch_bounds__(1024, 8) void k_labelprop_edges(hr_kargs a, R glab, R grp, R gcol,
                                                           int32_t* __restrict__ label,
                                                           const int32_t* __restrict__ rp,
                                                           const int32_t* __restrict__ col,
                                                           const uint8_t* __restrict__ mask,
-                                                          uint32_t n, uint32_t tpb, uint32_t vb)
+                                                          uint32_t n, uint32_t tpb, uint32_t vb,
+                                                          const lp_part* part)
 {
     extern __shared__ uint32_t smem[];
-    const uint32_t v0 = blockIdx.x * vb;
-    labelprop_edges<CHECK, G>(a.env, G{glab}, G{grp}, G{gcol}, label, rp, col, mask, n, tpb,
-                              v0, min(vb, n - v0), smem);
+    lp_share sh;
+    if (part) {
+        sh = lp_share_of(part, rp, n, gridDim.x, blockIdx.x);
+    } else {
+        sh = lp_share{};
+        sh.v0 = blockIdx.x * vb;
+        sh.v1 = min(n, sh.v0 + vb);
+    }
+    sh.pilot = part && blockIdx.x < 512;   // about the blocks that start the launch
+    labelprop_edges<CHECK, G>(a.env, G{glab}, G{grp}, G{gcol}, label, rp, col, mask, n, tpb, sh, vb,
+                              smem);
 }
 
 // The checked kernels on 4-byte shadow words.
@@ -413,14 +433,16 @@ extern "C" hr_status hr_labelprop_check(hr_ctx c, uint32_t r_label, uint32_t r_r
     const hr_status st = hr_epoch_enter(c, hr_stream(c, stream), nullptr);
     if (st != HR_OK) return st;
     return hr_launch_labelprop(a, r_label, r_row_ptr, r_col, label_dev, row_ptr_dev, col_dev,
-                               mask_dev, n, tpb, hr_stream(c, stream));
+                               mask_dev, n, tpb, hr_lp_room(c, hr_stream(c, stream)),
+                               hr_stream(c, stream));
 }
 
-// Vertices per 1024-thread block: about 4,096 blocks (8 rounds of the resident
-// ones), within 32..256 (up to 1,024 above 2^30 vertices).  Fewer vertices spread the hubs over more blocks,
-// each of which costs a launch slot and a label round: 100,003 vertices take
-// 0.25 ms per checked launch with 32 vertices, 0.36 ms with 256; 2^22
-// vertices 3.8 ms with 32 and 3.0 ms with 256 (3.6 ms with 512).
+// Vertices per 1024-thread block where the blocks are cut by vertices: about
+// 4,096 blocks (8 rounds of the resident ones), within 32..256 (up to 1,024
+// above 2^30 vertices).  Fewer vertices spread the hubs over more blocks, each
+// of which costs a launch slot and a label round: 100,003 vertices take 0.25
+// ms per checked launch with 32 vertices, 0.36 ms with 256; 2^22 vertices 3.8
+// ms with 32 and 3.0 ms with 256 (3.6 ms with 512).
 static uint32_t labelprop_vertices_per_block(uint32_t n)
 {
     uint32_t vb = 32;
@@ -429,11 +451,27 @@ static uint32_t labelprop_vertices_per_block(uint32_t n)
     return vb;
 }
 
-// check: 0 plain, 1 checked, 2 checked with the access log.
+// Pieces of a launch over n vertices (0: cut by vertices).  Jobs of 10
+// launches, 8 edges a vertex, in us: below 2,048 vertices the launch that cuts
+// costs more than it gives (1,000 vertices 249 cut by vertices, 264 in
+// pieces; 2,000 vertices 312 and 270).  Smaller pieces balance better, but
+// every block in flight can find a hub's word unsettled: 8,200 vertices 330
+// with 64 pieces, 406 with 16; 32,800: 468 with 128, 494 with 256; 100,003:
+// 688 with 195, 830 with 781; 2^20: 2,130 with 1,024, 2,240 with 2,048.
+static uint32_t labelprop_pieces(uint32_t n)
+{
+    if (n < 2048) return 0;
+    return std::min(HR_LP_PIECES,
+                    std::max({std::min(n / 128, 96u), std::min(n / 512, 256u), n / 1024}));
+}
+
+// check: 0 plain, 1 checked, 2 checked with the access log.  part: room for
+// HR_LP_PIECES + 1 entries that no other launch uses meanwhile, or NULL.
 template <class R, class G>
 static hr_status launch_labelprop(int check, const hr_kargs& a, R glab, R grp, R gcol,
                                   int32_t* label, const int32_t* rp, const int32_t* col,
-                                  const uint8_t* mask, uint32_t n, uint32_t tpb, hipStream_t s)
+                                  const uint8_t* mask, uint32_t n, uint32_t tpb, lp_part* part,
+                                  hipStream_t s)
 {
     if (a.env.group) {
         auto k = check == 2 ? k_labelprop<2, R, G> : k_labelprop<1, R, G>;
@@ -441,19 +479,26 @@ static hr_status launch_labelprop(int check, const hr_kargs& a, R glab, R grp, R
                   mask, n);
         return HR_OK;
     }
-    const uint32_t vb = labelprop_vertices_per_block(n);
     auto k = check == 0   ? k_labelprop_edges<0, R, G>
              : check == 1 ? k_labelprop_edges<1, R, G>
                           : k_labelprop_edges<2, R, G>;
-    HR_LAUNCH(k, dim3((n - 1) / vb + 1), dim3(1024), labelprop_lds_words(vb) * 4, s, a, glab, grp,
-              gcol, label, rp, col, mask, n, tpb, vb);
+    const uint32_t pieces = part ? labelprop_pieces(n) : 0;
+    uint32_t vb = labelprop_vertices_per_block(n), grid = (n - 1) / vb + 1;
+    if (pieces) {
+        vb = 1024;
+        grid = pieces;
+        HR_LAUNCH(k_labelprop_cut, dim3(pieces / 4 + 1), dim3(256), 0, s, part, label, rp, n,
+                  pieces);
+    }
+    HR_LAUNCH(k, dim3(grid), dim3(1024), labelprop_lds_words(vb) * 4, s, a, glab, grp, gcol, label,
+              rp, col, mask, n, tpb, vb, pieces ? part : nullptr);
     return HR_OK;
 }
 
 hr_status hr_launch_labelprop(const hr_kargs& a, uint32_t r_label, uint32_t r_row_ptr,
                               uint32_t r_col, int32_t* label_dev, const int32_t* row_ptr_dev,
                               const int32_t* col_dev, const uint8_t* mask_dev, uint32_t n,
-                              uint32_t tpb, hipStream_t s)
+                              uint32_t tpb, lp_part* part, hipStream_t s)
 {
     if (!label_dev || !row_ptr_dev || !col_dev || !mask_dev || !labelprop_shape_ok(n, tpb))
         return HR_E_INVAL;
@@ -465,13 +510,13 @@ hr_status hr_launch_labelprop(const hr_kargs& a, uint32_t r_label, uint32_t r_ro
         return launch_labelprop<hr_gref4, hr_gref4_1d<0>>(
             log ? 2 : 1, a, gref4(a, r_label), r_row_ptr != UINT32_MAX ? gref4(a, r_row_ptr) : none,
             r_col != UINT32_MAX ? gref4(a, r_col) : none, label_dev, row_ptr_dev, col_dev, mask_dev,
-            n, tpb, s);
+            n, tpb, part, s);
     }
     const hr_gref none{nullptr, 0, 0};
     return launch_labelprop<hr_gref, hr_gref_1d>(
         log ? 2 : 1, a, gref(a, r_label), r_row_ptr != UINT32_MAX ? gref(a, r_row_ptr) : none,
         r_col != UINT32_MAX ? gref(a, r_col) : none, label_dev, row_ptr_dev, col_dev, mask_dev, n,
-        tpb, s);
+        tpb, part, s);
 }
 
 extern "C" hr_status hr_labelprop_plain(int32_t* label_dev, const int32_t* row_ptr_dev,
@@ -482,7 +527,7 @@ extern "C" hr_status hr_labelprop_plain(int32_t* label_dev, const int32_t* row_p
         return HR_E_INVAL;
     return launch_labelprop<hr_gref, hr_gref_1d>(0, hr_kargs{}, hr_gref{}, hr_gref{}, hr_gref{},
                                                  label_dev, row_ptr_dev, col_dev, mask_dev, n, tpb,
-                                                 (hipStream_t)stream);
+                                                 nullptr, (hipStream_t)stream);
 }
 
 extern "C" hr_status hr_program_check(hr_ctx c, const uint32_t* regions_host, uint32_t n_regions,
