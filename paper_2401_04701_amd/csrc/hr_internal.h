@@ -3,6 +3,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "hr.h"
@@ -35,6 +37,28 @@ struct hr_region {
 };
 
 
+// Host memory that grows with use and is kept until its owner goes; its
+// contents are kept as far as asked for.
+struct hr_host_buf {
+    void* p = nullptr;
+    size_t size = 0;
+    hr_host_buf() = default;
+    hr_host_buf(const hr_host_buf&) = delete;
+    hr_host_buf& operator=(const hr_host_buf&) = delete;
+    ~hr_host_buf() { std::free(p); }
+    void* get(size_t bytes, size_t keep = 0)
+    {
+        if (bytes <= size) return p;
+        void* q = std::malloc(bytes);
+        if (!q) return nullptr;
+        if (keep) std::memcpy(q, p, keep);
+        std::free(p);
+        p = q;
+        size = bytes;
+        return p;
+    }
+};
+
 struct hr_ctx_s {
     hipStream_t stream;
     int device;
@@ -60,6 +84,7 @@ struct hr_ctx_s {
     // counters, in their allocation) and the stream that used it last.
     bool lp_used = false;
     hipStream_t lp_stream = nullptr;
+    hr_host_buf h_ring, h_keys;      // hr_report's copy of the ring and its sort
 };
 
 // Account for a checked launch on `s` in the current launch epoch.  *excl
@@ -104,8 +129,13 @@ void hr_free_alloc(hr_ctx c, uint32_t alloc);
 hipError_t hr_fill64(uint64_t* p, size_t n, hipStream_t s);
 hipError_t hr_fill32(uint32_t* p, size_t n, hipStream_t s);
 // Sort race records by key (space, region, block if LDS, index) and keep
-// the first of each key, in place; returns the number kept.
+// the first of each key, in place and without any allocation; returns the
+// number kept.
 size_t hr_sort_unique(hr_race* recs, size_t n);
+// The same from recs to out (cap records; only counted when they do not fit
+// or out is null), with `work` as room; false: no memory for it.
+bool hr_sort_records(const hr_race* recs, size_t n, hr_race* out, size_t cap, hr_host_buf& work,
+                     size_t* n_out);
 // Append a scanned record to ring[] for every race-state word among the
 // shadow words [first, first + n) of a region (4-byte words when word4),
 // taking slots from *count; ring must have room for n more records.  With

@@ -343,7 +343,6 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
     arena_alloc arena(arena_granules);
     std::vector<uint32_t> free_slots;
     for (uint32_t k = max_slots; k-- > 0;) free_slots.push_back(k);
-    std::vector<hr_race> ring(c->cfg.ring_capacity);
     uint32_t next = 0, finished = 0;
     uint64_t resident_items = 0;   // items of one phase of every resident job
     const auto t0 = clock_t_::now();
@@ -451,12 +450,15 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
             progressed = true;
             const uint32_t head = L.h_ctr[HR_CTR_HEAD], flags = L.h_ctr[HR_CTR_FLAGS];
             const uint32_t got = std::min(head, c->cfg.ring_capacity);
-            if (got && (hipMemcpyAsync(ring.data(), L.ring, sizeof(hr_race_rec) * got,
-                                       hipMemcpyDeviceToHost, L.s) != hipSuccess ||
-                        hipStreamSynchronize(L.s) != hipSuccess))
-                return HR_E_HIP;
-            // the descriptors carry 2*job (+1) as report ids
-            all.insert(all.end(), ring.begin(), ring.begin() + got);
+            if (got) {
+                // the descriptors carry 2*job (+1) as report ids
+                all.resize(all.size() + got);
+                if (hipMemcpyAsync(all.data() + all.size() - got, L.ring,
+                                   sizeof(hr_race_rec) * got, hipMemcpyDeviceToHost,
+                                   L.s) != hipSuccess ||
+                    hipStreamSynchronize(L.s) != hipSuccess)
+                    return HR_E_HIP;
+            }
             int warn = 0;
             if (flags & HR_DEVF_CLOCK) warn |= HR_W_CLOCK_OVERFLOW;
             if (flags & HR_DEVF_RANGE) warn |= HR_W_OUT_OF_RANGE;

@@ -356,6 +356,12 @@ def peak_load(words, scatter, sink, stream=None):
                                              _stream_ptr(stream)))
 
 
+def _report_cap(ring_capacity):
+    """Records to make room for at a report: the whole ring (its pages are
+    touched only as far as records are written), up to 100 MB."""
+    return max(4096, min(ring_capacity or 65536, 1 << 21))
+
+
 class DeviceProgram:
     """One launch of an access program, uploaded to device memory."""
 
@@ -399,6 +405,7 @@ class Context:
         cfg = _Config(ring_capacity, bc_bits, wc_bits, flags, shadow_budget, site_limit,
                       wave_bits, thread_bits, coalesce_width, log_capacity, 0)
         self.wave_bits = wave_bits or 6
+        self._cap = _report_cap(ring_capacity)
         self._c = ctypes.c_void_p(0)
         self._stream = _stream_ptr(stream)
         _check("hr_ctx_create", _lib.hr_ctx_create(ctypes.byref(self._c), ctypes.byref(cfg),
@@ -460,9 +467,9 @@ class Context:
     def report(self, stream=None):
         """Flagged records (RACE_DTYPE array) and the warning bits."""
         n = ctypes.c_size_t(0)
-        cap = 4096
+        cap = self._cap
         while True:
-            out = np.zeros(cap, dtype=RACE_DTYPE)
+            out = np.empty(cap, dtype=RACE_DTYPE)
             st = _lib.hr_report(self._c, out.ctypes.data_as(ctypes.c_void_p), cap,
                                 ctypes.byref(n), _stream_ptr(stream))
             if st == HR_E_INVAL and n.value > cap:
@@ -473,10 +480,7 @@ class Context:
             return out[:n.value], st
 
     def flagged(self, stream=None) -> set:
-        recs, _ = self.report(stream)
-        return {(int(r["space"]), int(r["region"]),
-                 int(r["block"]) if r["space"] == HR_LDS else 0, int(r["index"]))
-                for r in recs}
+        return _races_to_keys(self.report(stream)[0])
 
     def check_count(self, stream=None) -> int:
         out = ctypes.c_uint64(0)
@@ -534,9 +538,15 @@ class Context:
             _dptr(prog.ops), prog.n_ops, _dptr(block_map), lds_words, _stream_ptr(stream)))
 
 
+def _key_rows(recs):
+    """The records' keys (space, region, block if LDS else 0, index), in order."""
+    block = np.where(recs["space"] == HR_LDS, recs["block"], 0)
+    return zip(recs["space"].tolist(), recs["region"].tolist(), block.tolist(),
+               recs["index"].tolist())
+
+
 def _races_to_keys(recs):
-    return {(int(r["space"]), int(r["region"]),
-             int(r["block"]) if r["space"] == HR_LDS else 0, int(r["index"])) for r in recs}
+    return set(_key_rows(recs))
 
 
 def job_run(inst: Instance, ring_capacity=0, stream=None, static=False, site_limit=0,
@@ -549,9 +559,9 @@ def job_run(inst: Instance, ring_capacity=0, stream=None, static=False, site_lim
     fn_name = "hr_job_run_static" if static else "hr_job_run"
     fn = getattr(_lib, fn_name)
     n = ctypes.c_size_t(0)
-    cap = 4096
+    cap = _report_cap(ring_capacity)      # a larger count re-runs the job
     while True:
-        out = np.zeros(cap, dtype=RACE_DTYPE)
+        out = np.empty(cap, dtype=RACE_DTYPE)
         st = fn(ctypes.byref(inst), ctypes.byref(cfg), out.ctypes.data_as(ctypes.c_void_p), cap,
                 ctypes.byref(n), _stream_ptr(stream))
         if st == HR_E_INVAL and n.value > cap:
@@ -583,7 +593,7 @@ def serve(ctx: Context, instances, arrivals, shadow_budget=0, max_slots=0, seria
     cnt = ctypes.c_size_t(0)
     cap = 1 << 20          # a larger count re-runs the whole stream
     while True:
-        out = np.zeros(cap, dtype=RACE_DTYPE)
+        out = np.empty(cap, dtype=RACE_DTYPE)
         st = _lib.hr_serve(ctx.handle, inst, times, n, ctypes.byref(cfg),
                            out.ctypes.data_as(ctypes.c_void_p), cap, ctypes.byref(cnt),
                            _stream_ptr(stream))
@@ -593,11 +603,8 @@ def serve(ctx: Context, instances, arrivals, shadow_budget=0, max_slots=0, seria
         _check("hr_serve", st)
         break
     per = [set() for _ in range(n)]
-    for r in out[:cnt.value]:
-        j, k = divmod(int(r["region"]), 2)
-        lds = r["space"] == HR_LDS
-        per[j].add((int(r["space"]), 0 if lds else k, int(r["block"]) if lds else 0,
-                    int(r["index"])))
+    for space, region, block, index in _key_rows(out[:cnt.value]):
+        per[region >> 1].add((space, 0 if space == HR_LDS else region & 1, block, index))
     return per, times
 
 
