@@ -373,8 +373,8 @@ extern "C" hr_status hr_batch_create(hr_ctx c, hr_instance* inst, uint32_t n_ins
     if (hipMalloc(&b->d_inst, sizeof(hr_inst_dev) * n_inst) != hipSuccess ||
         hipMalloc(&b->d_items[0], sizeof(uint64_t) * q[0].size()) != hipSuccess ||
         hipMalloc(&b->d_items[1], sizeof(uint64_t) * q[1].size()) != hipSuccess ||
-        hipMalloc(&b->d_done, sizeof(uint32_t) * b->n_done) != hipSuccess ||
-        hipMalloc(&b->d_cursor, sizeof(uint32_t)) != hipSuccess) {
+        hipMalloc(&b->d_done, sizeof(uint32_t) * (b->n_done + 1)) != hipSuccess ||
+        hipMalloc(&b->d_cursor, 2 * sizeof(uint32_t)) != hipSuccess) {   // whole 8-byte words
         hr_batch_destroy(b);
         return HR_E_NOMEM;
     }
@@ -449,10 +449,10 @@ extern "C" hr_status hr_batch_run(hr_batch b, const hr_batch_tuning* tune, void*
         b->tile = t.tile;
     }
     // every run starts from initial shadow and empty phase counters
-    if (hr_fill64(c->allocs[b->arena].mem, c->allocs[b->arena].words, s) != hipSuccess ||
-        hr_fill32(b->d_done, b->n_done, s) != hipSuccess ||
-        hr_fill32(b->d_cursor, 1, s) != hipSuccess)
-        return HR_E_HIP;
+    const hr_piece pieces[] = {{c->allocs[b->arena].mem, c->allocs[b->arena].words},
+                               {b->d_done, (b->n_done + 1) / 2},
+                               {b->d_cursor, 1}};
+    if (hr_fill(pieces, 3, s) != hipSuccess) return HR_E_HIP;
     if (b->n_lp)
         HR_LAUNCH(k_batch_cut, dim3((b->n_part + 3) / 4), dim3(256), 0, s, b->d_inst, b->d_cut,
                   b->d_cut + b->n_lp, b->n_lp);

@@ -126,8 +126,15 @@ uint32_t hr_new_region(hr_ctx c, const void* data, size_t elems, uint64_t* shado
 // Shadow words of a region (tiles' padding included).
 size_t hr_region_words(const hr_region& r);
 void hr_free_alloc(hr_ctx c, uint32_t alloc);
-hipError_t hr_fill64(uint64_t* p, size_t n, hipStream_t s);
-hipError_t hr_fill32(uint32_t* p, size_t n, hipStream_t s);
+// Clear pieces of device memory (16-byte aligned, in 8-byte words) with as
+// few launches as fit.
+struct hr_piece {
+    void* mem;
+    size_t words;
+};
+hipError_t hr_fill(const hr_piece* pieces, size_t count, hipStream_t s);
+// The counter words as a piece (their allocation is padded, HR_CTR_BYTES).
+#define HR_CTR_PIECE(ctr) hr_piece{(ctr), (HR_CTR_WORDS + 1) / 2}
 // Sort race records by key (space, region, block if LDS, index) and keep
 // the first of each key, in place and without any allocation; returns the
 // number kept.

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <initializer_list>
 #include <new>
 #include <vector>
 
@@ -13,46 +14,84 @@
 
 namespace {
 
-__global__ void k_fill64(uint64_t* __restrict__ p, size_t n, uint64_t v)
-{
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = v;
-}
+// Clears and fills take several pieces of memory in one launch: a job's
+// start is a chain of launches, about 2 us each on the device however
+// little they clear.  16-byte stores over whole blocks of each piece.
+constexpr uint32_t SEGS = 8;
+struct segs {
+    uint64_t* p[SEGS];
+    size_t n[SEGS];      // 8-byte units; p is 16-byte aligned
+    uint32_t count;
+};
 
-__global__ void k_fill32(uint32_t* __restrict__ p, size_t n, uint32_t v)
+__global__ __launch_bounds__(256) void k_fill(segs g)
 {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = v;
+    for (uint32_t k = 0; k < g.count; ++k) {
+        ulonglong2* p = reinterpret_cast<ulonglong2*>(g.p[k]);
+        for (size_t i = t; i < g.n[k] / 2; i += stride) p[i] = make_ulonglong2(0, 0);
+        if (t == 0 && (g.n[k] & 1)) g.p[k][g.n[k] - 1] = 0;
+    }
 }
 
 // The launch-boundary clear of 4-byte words, two per 8-byte unit: back to
 // the initial state, except that while some race record is missing from the
 // ring (it overflowed, or a call site reached its record limit; read on the
 // device) a word in the race state keeps it for the report's scan.
-__global__ void k_clear_word4(uint64_t* __restrict__ p, size_t n, const uint32_t* __restrict__ ctr,
-                              uint32_t ring_cap)
+__global__ __launch_bounds__(256) void k_clear_word4(segs g, const uint32_t* __restrict__ ctr,
+                                                     uint32_t ring_cap)
 {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;
-    if (ctr[HR_CTR_HEAD] <= ring_cap && !(ctr[HR_CTR_FLAGS] & HR_DEVF_LIMIT)) {
-        for (; i < n; i += stride) p[i] = 0;
-        return;
-    }
-    for (; i < n; i += stride) {
-        const uint64_t v = p[i];
+    const bool keep = ctr[HR_CTR_HEAD] > ring_cap || (ctr[HR_CTR_FLAGS] & HR_DEVF_LIMIT);
+    const auto left = [keep](uint64_t v) {
+        if (!keep) return (uint64_t)0;
         const uint64_t lo = (uint32_t)v == hr::T_RACE ? hr::T_RACE : 0u;
         const uint64_t hi = (uint32_t)(v >> 32) == hr::T_RACE ? hr::T_RACE : 0u;
-        p[i] = lo | (hi << 32);
+        return lo | (hi << 32);
+    };
+    for (uint32_t k = 0; k < g.count; ++k) {
+        ulonglong2* p = reinterpret_cast<ulonglong2*>(g.p[k]);
+        for (size_t i = t; i < g.n[k] / 2; i += stride) {
+            const ulonglong2 v = keep ? p[i] : make_ulonglong2(0, 0);
+            p[i] = make_ulonglong2(left(v.x), left(v.y));
+        }
+        uint64_t* last = g.p[k] + g.n[k] - 1;
+        if (t == 0 && (g.n[k] & 1)) *last = left(keep ? *last : 0);
     }
 }
 
-hr_status clear_shadows(hr_ctx c, hipStream_t s)
+// Launch `kern` over pieces of memory, SEGS at a time.
+template <class K, class... A>
+hipError_t launch_segs(K kern, const hr_piece* pieces, size_t count, hipStream_t s, A... args)
 {
+    for (size_t at = 0; at < count;) {
+        segs g{};
+        size_t most = 0;
+        for (; at < count && g.count < SEGS; ++at) {
+            if (pieces[at].words == 0) continue;
+            g.p[g.count] = (uint64_t*)pieces[at].mem;
+            g.n[g.count++] = pieces[at].words;
+            most = std::max(most, pieces[at].words);
+        }
+        if (g.count == 0) break;
+        const size_t blocks = std::min<size_t>((most + 511) / 512, 4096);
+        (void)hipGetLastError();   // drop stale errors of unrelated earlier calls
+        hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, g, args...);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// The shadow allocations of a context, after `head`.
+std::vector<hr_piece> shadow_pieces(hr_ctx c, std::initializer_list<hr_piece> head = {})
+{
+    std::vector<hr_piece> v(head);
     for (const hr_alloc& al : c->allocs)
-        if (al.live && hr_fill64(al.mem, al.words, s) != hipSuccess) return HR_E_HIP;
-    return HR_OK;
+        if (al.live) v.push_back({al.mem, al.words});
+    return v;
 }
 
 // The global races among n shadow words: each word in the race state is
@@ -206,22 +245,9 @@ hipError_t hr_scan_races_dev(const uint64_t* sh, size_t n, size_t first, bool wo
 
 // Clears run as kernels rather than hipMemsetAsync so the calls stay safe
 // inside a captured HIP graph.
-hipError_t hr_fill64(uint64_t* p, size_t n, hipStream_t s)
+hipError_t hr_fill(const hr_piece* pieces, size_t count, hipStream_t s)
 {
-    if (n == 0) return hipSuccess;
-    const size_t blocks = std::min<size_t>((n + 255) / 256, 8192);
-    (void)hipGetLastError();   // drop stale errors of unrelated earlier calls
-    hipLaunchKernelGGL(k_fill64, dim3((unsigned)blocks), dim3(256), 0, s, p, n, 0ull);
-    return hipGetLastError();
-}
-
-hipError_t hr_fill32(uint32_t* p, size_t n, hipStream_t s)
-{
-    if (n == 0) return hipSuccess;
-    const size_t blocks = std::min<size_t>((n + 255) / 256, 1024);
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(k_fill32, dim3((unsigned)blocks), dim3(256), 0, s, p, n, 0u);
-    return hipGetLastError();
+    return launch_segs(k_fill, pieces, count, s);
 }
 
 hipStream_t hr_stream(hr_ctx c, void* stream)
@@ -332,7 +358,8 @@ hr_status hr_new_alloc(hr_ctx c, size_t words, uint32_t* alloc_out)
     if (c->cfg.shadow_budget && c->shadow_bytes + bytes > c->cfg.shadow_budget) return HR_E_NOMEM;
     uint64_t* mem = nullptr;
     if (hipMalloc(&mem, bytes) != hipSuccess) return HR_E_NOMEM;
-    if (hr_fill64(mem, words, c->stream) != hipSuccess) {
+    const hr_piece piece{mem, words};
+    if (hr_fill(&piece, 1, c->stream) != hipSuccess) {
         (void)hipFree(mem);
         return HR_E_HIP;
     }
@@ -449,8 +476,8 @@ extern "C" hr_status hr_ctx_create(hr_ctx* out, const hr_config* cfg, void* stre
         hr_ctx_destroy(c);
         return HR_E_HIP;
     }
-    if (hr_fill32(c->ctr, HR_CTR_WORDS, c->stream) != hipSuccess ||
-        hr_fill64((uint64_t*)c->count, HR_COUNT_SLOTS, c->stream) != hipSuccess) {
+    const hr_piece pieces[] = {HR_CTR_PIECE(c->ctr), {c->count, HR_COUNT_SLOTS}};
+    if (hr_fill(pieces, 2, c->stream) != hipSuccess) {
         hr_ctx_destroy(c);
         return HR_E_HIP;
     }
@@ -582,12 +609,10 @@ extern "C" hr_status hr_kernel_end(hr_ctx c, void* stream)
     if (c->cfg.flags & HR_CFG_WORD4) {
         // No launch field: every boundary returns the words to INIT.
         hipStream_t s = hr_stream(c, stream);
-        for (const hr_alloc& al : c->allocs) {
-            if (!al.live || al.words == 0) continue;
-            const size_t blocks = std::min<size_t>((al.words + 255) / 256, 8192);
-            HR_LAUNCH(k_clear_word4, dim3((unsigned)blocks), dim3(256), 0, s, al.mem, al.words,
-                      c->ctr, c->cfg.ring_capacity);
-        }
+        const std::vector<hr_piece> v = shadow_pieces(c);
+        if (launch_segs(k_clear_word4, v.data(), v.size(), s, (const uint32_t*)c->ctr,
+                        c->cfg.ring_capacity) != hipSuccess)
+            return HR_E_HIP;
         return HR_OK;
     }
     // The launch epoch in a shadow word has 9 bits: before it wraps, return
@@ -606,7 +631,9 @@ extern "C" hr_status hr_kernel_end(hr_ctx c, void* stream)
             const hr_status st = scan_races(c, c->carried);
             if (st != HR_OK) return st;
         }
-        return clear_shadows(c, s);
+        const std::vector<hr_piece> v = shadow_pieces(c);
+        if (hr_fill(v.data(), v.size(), s) != hipSuccess) return HR_E_HIP;
+        return HR_OK;
     }
     return HR_OK;
 }
@@ -615,10 +642,9 @@ extern "C" hr_status hr_reset(hr_ctx c, void* stream)
 {
     if (!c) return HR_E_INVAL;
     hipStream_t s = hr_stream(c, stream);
-    hr_status st = clear_shadows(c, s);
-    if (st != HR_OK) return st;
-    if (hr_fill32(c->ctr, HR_CTR_WORDS, s) != hipSuccess) return HR_E_HIP;
-    if (hr_fill64((uint64_t*)c->count, HR_COUNT_SLOTS, s) != hipSuccess) return HR_E_HIP;
+    const std::vector<hr_piece> v =
+        shadow_pieces(c, {HR_CTR_PIECE(c->ctr), {c->count, HR_COUNT_SLOTS}});
+    if (hr_fill(v.data(), v.size(), s) != hipSuccess) return HR_E_HIP;
     c->launch_seq = 0;
     c->carried.clear();
     epoch_begin(c);

@@ -268,7 +268,7 @@ hr_status lane_init(lane_state& L, hr_ctx c, hipStream_t caller, bool first, uin
         L.own_ring = true;
         if (hipMalloc(&L.ring, sizeof(hr_race_rec) * std::max(1u, c->cfg.ring_capacity)) !=
                 hipSuccess ||
-            hipMalloc(&L.ctr, sizeof(uint32_t) * HR_CTR_WORDS) != hipSuccess)
+            hipMalloc(&L.ctr, HR_CTR_BYTES) != hipSuccess)
             return HR_E_NOMEM;
     }
     if (hipEventCreateWithFlags(&L.done, hipEventDisableTiming) != hipSuccess) return HR_E_HIP;
@@ -362,7 +362,8 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
             lane_state& L = b.lane[lane_of_job[next]];
             uint64_t* sh0 = b.arena + off * GRANULE_WORDS;
             uint64_t* sh1 = st.elems[1] ? sh0 + st.elems[0] : nullptr;
-            if (hr_fill64(sh0, st.elems[0] + st.elems[1], L.s) != hipSuccess) return HR_E_HIP;
+            const hr_piece words{sh0, st.elems[0] + st.elems[1]};
+            if (hr_fill(&words, 1, L.s) != hipSuccess) return HR_E_HIP;
             b.h_desc[st.slot] = hr_make_inst_dev(st.in, st.elems, sh0, sh1, 2 * next, 2 * next + 1, 0);
             if (st.in.pattern == HR_PAT_LABELPROP) b.h_desc[st.slot].part = b.part + st.part;
             if (hipMemcpyAsync(b.slots + st.slot, b.h_desc + st.slot, sizeof(hr_inst_dev),
@@ -378,7 +379,8 @@ hr_status serve_continuous(hr_ctx c, const hr_instance* jobs, hr_serve_job* time
             lane_state& L = b.lane[k];
             if (L.in_flight || L.jobs.empty()) continue;
             const size_t n_run = k == LANE_LARGE ? 1 : L.jobs.size();
-            if (hr_fill32(L.ctr, HR_CTR_WORDS, L.s) != hipSuccess) return HR_E_HIP;
+            const hr_piece ctr = HR_CTR_PIECE(L.ctr);
+            if (hr_fill(&ctr, 1, L.s) != hipSuccess) return HR_E_HIP;
             job_state& first = js[L.jobs[0]];
             if (k == LANE_LARGE && first.in.pattern == HR_PAT_JACOBI) {
                 // its next phases, one launch of the stencil kernel each

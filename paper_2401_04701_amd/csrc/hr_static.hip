@@ -81,13 +81,13 @@ extern "C" hr_status hr_job_run_static(const hr_instance* inst, const hr_config*
     uint32_t* ctr = (uint32_t*)(base + OFF_CTR);
     unsigned long long* count = (unsigned long long*)(base + OFF_COUNT);
     uint32_t* scan_n = (uint32_t*)(base + OFF_SCAN);
+    const hr_piece scan_piece{scan_n, 1};
     hr_race_rec* ring = (hr_race_rec*)(base + OFF_RING);
     uint64_t* sh[2] = {(uint64_t*)(base + OFF_SHADOW), (uint64_t*)(base + OFF_SHADOW) + el[0]};
 
     // The previous call's contents stay in the array: start from zero.
-    HR_HIP_CHECK(hr_fill32(ctr, HR_CTR_WORDS, s));
-    HR_HIP_CHECK(hr_fill64((uint64_t*)count, HR_COUNT_SLOTS, s));
-    HR_HIP_CHECK(hr_fill64(sh[0], el[0] + el[1], s));
+    const hr_piece pieces[] = {HR_CTR_PIECE(ctr), {count, HR_COUNT_SLOTS}, {sh[0], el[0] + el[1]}};
+    HR_HIP_CHECK(hr_fill(pieces, 3, s));
 
     hr_kargs a{};
     for (int r = 0; r < 2; ++r) {
@@ -143,7 +143,7 @@ extern "C" hr_status hr_job_run_static(const hr_instance* inst, const hr_config*
     const bool scan = head > k.ring_capacity || (flags & HR_DEVF_LIMIT);
     size_t n_scan = 0;
     if (scan) {   // count the race words first, to size the result
-        HR_HIP_CHECK(hr_fill32(scan_n, 1, s));
+        HR_HIP_CHECK(hr_fill(&scan_piece, 1, s));
         for (uint32_t r = 0; r < 2; ++r)
             HR_HIP_CHECK(hr_scan_races_dev(sh[r], el[r], 0, false, r, nullptr, scan_n, s));
         HR_HIP_CHECK(hipStreamSynchronize(s));
@@ -166,7 +166,7 @@ extern "C" hr_status hr_job_run_static(const hr_instance* inst, const hr_config*
         const size_t chunk = k.ring_capacity;
         for (uint32_t r = 0; r < 2; ++r) {
             for (size_t first = 0; first < el[r]; first += chunk) {
-                HR_HIP_CHECK(hr_fill32(scan_n, 1, s));
+                HR_HIP_CHECK(hr_fill(&scan_piece, 1, s));
                 HR_HIP_CHECK(hr_scan_races_dev(sh[r], std::min(chunk, el[r] - first), first, false,
                                                r, ring, scan_n, s));
                 HR_HIP_CHECK(hipStreamSynchronize(s));
