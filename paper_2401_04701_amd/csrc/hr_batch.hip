@@ -32,6 +32,16 @@ __device__ __forceinline__ uint64_t claim(uint32_t* cursor, const uint64_t* item
     return i < n_items ? items[i] : ~0ull;
 }
 
+// Phases hand over without cache maintenance: everything that a phase writes
+// and a later one reads (cells, labels, shadow words, pieces' labels) is
+// written and read with agent-scope operations, which act past the L2s of
+// the chip's dies, so a phase is complete for the others once its waves'
+// stores are (this wait) and the counter then says so.  A release and an
+// acquire at agent scope per item, which write back and invalidate a whole
+// L2 under the 31 workers beside it, made a stencil item of four tiles 33 us
+// and a label-propagation item 100 us.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Jobs whose pieces' labels are renewed between phases.
 __device__ __forceinline__ bool renews(const hr_inst_dev& I)
 {
@@ -86,8 +96,6 @@ __device__ __forceinline__ void batch_loop(const hr_env& base, const hr_inst_dev
         if (threadIdx.x == 0) {
             uint32_t go = 1;
             if (phase > 0) {
-                // (relaxed: an acquire at every poll would invalidate the
-                // caches under the workers that are being waited for)
                 const uint32_t* d = done + I.done_off + phase - 1;
                 const uint32_t all = I.items + (renews(I) ? 1u : 0u);
                 uint32_t spins = 0;
@@ -103,25 +111,23 @@ __device__ __forceinline__ void batch_loop(const hr_env& base, const hr_inst_dev
             s_go = go;
         }
         __syncthreads();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         if (uni(s_go)) {
             hr_env e = base;
             e.launch = phase & ((1u << hr::g::LAUNCH_BITS) - 1);
             e.launch_seq = phase;
-            run_item(e, I, phase, item, smem);
+            run_item<HR_ALL_PATTERNS, true>(e, I, phase, item, smem);
         }
+        stores_done();
         __syncthreads();                                // every hook of the item is done
         uint32_t* const d = done + I.done_off + phase;
         if (threadIdx.x == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            s_go = __hip_atomic_fetch_add(d, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            s_go = __hip_atomic_fetch_add(d, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_item = claim(cursor, items, n_items);
         }
         __syncthreads();
         if (renews(I) && uni(s_go) + 1 == I.items) {
             // the phase's last item: the labels that the next phase's pieces
             // continue with (it waits for one count more)
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             for (uint32_t i = threadIdx.x; i <= I.items; i += blockDim.x) {
                 const uint32_t v = I.part[i].v;
                 if (v)
@@ -131,11 +137,10 @@ __device__ __forceinline__ void batch_loop(const hr_env& base, const hr_inst_dev
                                                          __HIP_MEMORY_SCOPE_AGENT),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+            stores_done();
             __syncthreads();
-            if (threadIdx.x == 0) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                __hip_atomic_fetch_add(d, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            if (threadIdx.x == 0)
+                __hip_atomic_fetch_add(d, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __syncthreads();
         }
     }

@@ -113,6 +113,17 @@ __device__ void reduce_body(const hr_env& e, const G& gin, const G& gout,
 // launch: on R-MAT graphs of 50 K to 250 K vertices it holds 80 K to 180 K
 // edges, 6 us a round of 1024.
 
+// A seeded edge's plain read and write of a label, past the caches: a batch's
+// workers run several sweeps with only a counter between them.
+__device__ __forceinline__ int32_t lp_get(const int32_t* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void lp_set(int32_t* p, int32_t v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Where piece i of a job begins: its first vertex v, its first edge
 // i * length - v, and, when that edge belongs to vertex v - 1, that vertex's
 // label.
@@ -293,9 +304,9 @@ __device__ __forceinline__ void labelprop_edges(const hr_env& e, const G& glab, 
                 hr_gs<0, CHECK>(e, th, gcol, pc, (uint64_t)k, HR_SITE_LP_CSR);
             hr_gs<2, CHECK>(e, th, glab, pu, u, HR_SITE_LP_MIN);
             if (u < n && seeded) {
-                const int32_t r = label[u];
+                const int32_t r = lp_get(label + u);
                 hr_gpre<0, CHECK, false>(e, th, glab, u, HR_SITE_LP_SEED_READ, q);
-                label[u] = r < l ? r : l;
+                lp_set(label + u, r < l ? r : l);
                 hr_g<1, CHECK>(e, th, glab, u, HR_SITE_LP_SEED_WRITE);
             }
         }
@@ -348,9 +359,9 @@ __device__ void labelprop_body(const hr_env& e, const G& glab, const G& grp, con
         if (CHECK && gcol.shadow) hr_g<0, CHECK>(e, th, gcol, (uint64_t)k, HR_SITE_LP_CSR);
         if (u >= n) continue;
         if (seeded) {
-            const int32_t r = label[u];
+            const int32_t r = lp_get(label + u);
             hr_gpre<0, CHECK>(e, th, glab, u, HR_SITE_LP_SEED_READ, su);
-            label[u] = r < l ? r : l;
+            lp_set(label + u, r < l ? r : l);
             hr_g<1, CHECK, true>(e, th, glab, u, HR_SITE_LP_SEED_WRITE);
         } else {
             atomicMin(label + u, l);

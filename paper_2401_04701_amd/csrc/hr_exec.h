@@ -64,7 +64,10 @@ __device__ __forceinline__ hr_gref uni_gref(const hr_gref& g)
 constexpr uint32_t HR_ALL_PATTERNS = (1u << HR_PAT_REDUCE) | (1u << HR_PAT_JACOBI) |
                                      (1u << HR_PAT_LABELPROP);
 
-template <uint32_t PATTERNS = HR_ALL_PATTERNS>
+//
+// COH: the phases of a job follow each other within the launch (the batch):
+// what one phase writes and a later one reads goes past the caches.
+template <uint32_t PATTERNS = HR_ALL_PATTERNS, bool COH = false>
 __device__ __forceinline__ void run_item(const hr_env& e, const hr_inst_dev& I, uint32_t phase,
                                          uint32_t item, uint32_t* smem)
 {
@@ -90,9 +93,9 @@ __device__ __forceinline__ void run_item(const hr_env& e, const hr_inst_dev& I, 
             const bool odd = phase & 1u;
             const float* uo = (const float*)(odd ? I.p1 : I.p0);
             float* un = (float*)(odd ? I.p0 : I.p1);
-            jacobi_body<1>(e, odd ? I.g1 : I.g0, odd ? I.g0 : I.g1, uo, un, I.ny, I.n, I.nbx,
-                              (const int32_t*)I.p2, lb, t, (float*)lds, lds + JACOBI_TILE_WORDS,
-                              I.lds_id);
+            jacobi_body<1, hr_gref, hr_block_sync, COH>(
+                e, odd ? I.g1 : I.g0, odd ? I.g0 : I.g1, uo, un, I.ny, I.n, I.nbx,
+                (const int32_t*)I.p2, lb, t, (float*)lds, lds + JACOBI_TILE_WORDS, I.lds_id);
             return;
         }
     }

@@ -73,6 +73,9 @@ struct hr_tile_sync {
 // the LDS tile's words the staging writes and then every read of them.  Each
 // global word is loaded once, with the data, and stored once.
 //
+// COH: the cells are read and written past the caches (agent scope), for a
+// kernel whose blocks run several sweeps with only a counter between them.
+//
 // What bounds it: memory.  4096 x 4096: 0.150 ms per launch, 4.5 TB/s of the
 // 671 MB of grids and shadow words (a large copy reaches 4.9 TB/s here),
 // against 0.278 ms with every access published by its own thread's exchange
@@ -81,7 +84,7 @@ struct hr_tile_sync {
 // the closed forms (hr_own_fast), with their rare paths inside the kernel
 // and not at its end, took 0.184 ms, issue-bound; plain, nontemporal or
 // coherent loads and stores of the words made no difference.
-template <int CHECK, class G = hr_gref, class SYNC = hr_block_sync>
+template <int CHECK, class G = hr_gref, class SYNC = hr_block_sync, bool COH = false>
 __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
                             const float* __restrict__ uo, float* __restrict__ un, uint32_t ny,
                             uint32_t nx, uint32_t nbx, const int32_t* __restrict__ seeds,
@@ -97,6 +100,18 @@ __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
     constexpr uint32_t OLD = 1, CENTRE = 2, ROW = 4, COL = 8, NEW = 16;
     hr_thread th{};
     if constexpr (CHECK) th = hr_thread_make(e, lb, t);
+    const auto cell = [&](size_t i) {
+        if constexpr (COH)
+            return __hip_atomic_load(uo + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            return uo[i];
+    };
+    const auto set = [&](size_t i, float v) {
+        if constexpr (COH)
+            __hip_atomic_store(un + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            un[i] = v;
+    };
     const size_t g = (size_t)gy * nx + gx;
     const uint32_t cl = (ty + 1) * TL + tx + 1;
     // An edge thread stages at most one row halo cell (north or south) and
@@ -122,9 +137,9 @@ __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
     bool in_place = false;
     if constexpr (CHECK) in_place = gold.shadow == gnew.shadow;
     if (inside) {
-        const float vc = uo[g];
-        const float vr = hn || hs ? uo[gr] : 0.0f;
-        const float vk = hw || he ? uo[gc] : 0.0f;
+        const float vc = cell(g);
+        const float vr = hn || hs ? cell(gr) : 0.0f;
+        const float vk = hw || he ? cell(gc) : 0.0f;
         if constexpr (CHECK) {
             qo = hr_gload<CHECK>(th, gold, xo);
             if (!in_place) qn = hr_gload<CHECK>(th, gnew, xn);
@@ -193,7 +208,7 @@ __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
             if ((hw || he) && !hr_own_lds_fast<0>(e, th, tsh, lc, 0)) late |= COL;
         }
         const float r = 0.2f * (c + vn + vs + vw + ve);
-        un[g] = r;
+        set(g, r);
         if constexpr (CHECK) {
             if (e.count) hr_note<1, CHECK>(e, th, gnew, g, HR_SITE_JACOBI_OUT);
         }
@@ -207,7 +222,7 @@ __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
                 else if (side == 2 && tx == 0 && ty == off && gx > 0) tgt = g - 1;
                 else if (side == 3 && tx == 15 && ty == off && gx + 1 < nx) tgt = g + 1;
                 if (tgt != g) {
-                    un[tgt] = r;
+                    set(tgt, r);
                     if constexpr (CHECK) {
                         if (e.count) hr_note<1, CHECK>(e, th, gnew, tgt, HR_SITE_JACOBI_SEED);
                     }
