@@ -113,15 +113,21 @@ __device__ void reduce_body(const hr_env& e, const G& gin, const G& gout,
 // launch: on R-MAT graphs of 50 K to 250 K vertices it holds 80 K to 180 K
 // edges, 6 us a round of 1024.
 
-// A seeded edge's plain read and write of a label, past the caches: a batch's
-// workers run several sweeps with only a counter between them.
+// A seeded edge's plain read and write of a label.  COH: past the caches, for
+// a batch's workers, which run several sweeps with only a counter between
+// them.  (Elsewhere the caches take the write: 2^25 edges, 1 % seeded, 0.73 ms
+// per launch against 1.28 past them.)
+template <bool COH>
 __device__ __forceinline__ int32_t lp_get(const int32_t* p)
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (COH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return *p;
 }
+template <bool COH>
 __device__ __forceinline__ void lp_set(int32_t* p, int32_t v)
 {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if constexpr (COH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
 }
 
 // Where piece i of a job begins: its first vertex v, its first edge
@@ -223,7 +229,7 @@ __device__ __forceinline__ lp_share lp_share_of(const lp_part* part, const int32
 // registers (two 1024-thread blocks per compute unit), was as fast as 2 or 4
 // edges per lane (with more registers) and as loading the next edge's words
 // ahead.  vt: vertices loaded at a time.
-template <int CHECK, class G>
+template <int CHECK, class G, bool COH = false>
 __device__ __forceinline__ void labelprop_edges(const hr_env& e, const G& glab, const G& grp,
                                                 const G& gcol, int32_t* __restrict__ label,
                                                 const int32_t* __restrict__ rp,
@@ -304,9 +310,9 @@ __device__ __forceinline__ void labelprop_edges(const hr_env& e, const G& glab, 
                 hr_gs<0, CHECK>(e, th, gcol, pc, (uint64_t)k, HR_SITE_LP_CSR);
             hr_gs<2, CHECK>(e, th, glab, pu, u, HR_SITE_LP_MIN);
             if (u < n && seeded) {
-                const int32_t r = lp_get(label + u);
+                const int32_t r = lp_get<COH>(label + u);
                 hr_gpre<0, CHECK, false>(e, th, glab, u, HR_SITE_LP_SEED_READ, q);
-                lp_set(label + u, r < l ? r : l);
+                lp_set<COH>(label + u, r < l ? r : l);
                 hr_g<1, CHECK>(e, th, glab, u, HR_SITE_LP_SEED_WRITE);
             }
         }
@@ -324,7 +330,7 @@ constexpr uint32_t labelprop_lds_words(uint32_t vt) { return 3 * vt + 4; }
 // must run one logical wave per hardware wave (hr_group).  While edge k is
 // checked, the column index of edge k+2, and the seeded flag of edge k+1 and
 // the shadow word of its target, are already in flight.
-template <int CHECK, class G = hr_gref>
+template <int CHECK, class G = hr_gref, bool COH = false>
 __device__ void labelprop_body(const hr_env& e, const G& glab, const G& grp, const G& gcol,
                                int32_t* __restrict__ label, const int32_t* __restrict__ rp,
                                const int32_t* __restrict__ col, const uint8_t* __restrict__ mask,
@@ -359,9 +365,9 @@ __device__ void labelprop_body(const hr_env& e, const G& glab, const G& grp, con
         if (CHECK && gcol.shadow) hr_g<0, CHECK>(e, th, gcol, (uint64_t)k, HR_SITE_LP_CSR);
         if (u >= n) continue;
         if (seeded) {
-            const int32_t r = lp_get(label + u);
+            const int32_t r = lp_get<COH>(label + u);
             hr_gpre<0, CHECK>(e, th, glab, u, HR_SITE_LP_SEED_READ, su);
-            lp_set(label + u, r < l ? r : l);
+            lp_set<COH>(label + u, r < l ? r : l);
             hr_g<1, CHECK, true>(e, th, glab, u, HR_SITE_LP_SEED_WRITE);
         } else {
             atomicMin(label + u, l);

@@ -104,16 +104,18 @@ __device__ __forceinline__ void run_item(const hr_env& e, const hr_inst_dev& I, 
             using G = hr_gref_1d;
             const G none{};
             if (e.group) {   // uniform: an environment field
-                labelprop_body<1>(e, G{I.g0}, none, none, (int32_t*)I.p0, (const int32_t*)I.p1,
-                                  (const int32_t*)I.p2, (const uint8_t*)I.p3, I.n, T, lb, t);
+                labelprop_body<1, G, COH>(e, G{I.g0}, none, none, (int32_t*)I.p0,
+                                          (const int32_t*)I.p1, (const int32_t*)I.p2,
+                                          (const uint8_t*)I.p3, I.n, T, lb, t);
             } else {
                 lp_share sh = lp_share_of(I.part, (const int32_t*)I.p1, I.n, I.items, item);
                 // about the items that start a phase (a batch of 56 mixed jobs
                 // 7.3 ms without, 6.7 with)
                 sh.pilot = item < 512;
-                labelprop_edges<1>(e, G{I.g0}, none, none, (int32_t*)I.p0, (const int32_t*)I.p1,
-                                   (const int32_t*)I.p2, (const uint8_t*)I.p3, I.n, T, sh,
-                                   HR_WORKER_THREADS, smem);
+                labelprop_edges<1, G, COH>(e, G{I.g0}, none, none, (int32_t*)I.p0,
+                                           (const int32_t*)I.p1, (const int32_t*)I.p2,
+                                           (const uint8_t*)I.p3, I.n, T, sh, HR_WORKER_THREADS,
+                                           smem);
             }
         }
     }
