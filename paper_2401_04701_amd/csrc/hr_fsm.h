@@ -146,7 +146,9 @@ HR_HD bool fresh(uint64_t old, uint64_t id, uint32_t k, bool others, uint64_t* n
 {
     const uint32_t tag = (uint32_t)(old & TAG_M);
     *nw = others ? (mk(T_MB, 0, k, 0) | (id & LA_M)) : (mk(T_ST, k, k, k) | id);
-    return tag != T_RACE && (tag == T_INIT || ((old ^ id) & LA_M)) && !(others && k == CL_X);
+    // (no short circuits: each would be a branch)
+    const bool later = (uint32_t)((old ^ id) >> LA_SH) != 0;
+    return (tag != T_RACE) & ((tag == T_INIT) | later) & !(others & (k == CL_X));
 }
 
 // ---------------------------------------------------------------------------
@@ -572,7 +574,8 @@ HR_HD bool fresh(uint32_t old, uint32_t id, uint32_t k, uint32_t others, uint32_
     *nw = others == 0   ? (mk(T_ST, k, k) | id)
           : others == 1 ? (mk(T_MT, k, k) | (id & (BC_M | wm | WC_M)))
                         : (mk(T_MW, k, 0) | (id & BC_M));
-    return tag != T_RACE && (tag == T_INIT || ((old ^ id) & BC_M)) && !(others && k == CL_X);
+    return (tag != T_RACE) & ((tag == T_INIT) | (((old ^ id) & BC_M) != 0)) &
+           !((others != 0) & (k == CL_X));
 }
 }  // namespace l
 

@@ -368,10 +368,11 @@ __device__ __forceinline__ bool hr_own_fast(const hr_env& e, const hr_thread& t,
 {
     typename G::word nw;
     const bool ok = hr_own_fresh<KIND>(e, t, g, old, b, c, &nw);
-    if (!e.excl || !ok || t.enabled != 1) return !g.shadow;
-    if (g.shadow)
-        __hip_atomic_store(g.shadow + x.off, nw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
+    if (!g.shadow) return true;
+    if (!e.excl) return false;
+    const bool done = ok & (t.enabled == 1);
+    if (done) __hip_atomic_store(g.shadow + x.off, nw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return done;
 }
 
 // The owner update of element x: the owner's own access, then b and c, all

@@ -76,7 +76,7 @@ struct hr_tile_sync {
 // COH: the cells are read and written past the caches (agent scope), for a
 // kernel whose blocks run several sweeps with only a counter between them.
 //
-// What bounds it: memory.  4096 x 4096: 0.150 ms per launch, 4.5 TB/s of the
+// What bounds it: memory.  4096 x 4096: 0.143 ms per launch, 4.7 TB/s of the
 // 671 MB of grids and shadow words (a large copy reaches 4.9 TB/s here),
 // against 0.278 ms with every access published by its own thread's exchange
 // (100 memory-side requests per tile, which run at 25 G/s on the chip, and
@@ -170,10 +170,10 @@ __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
     sync.template bar<CHECK>(e, th);
     // the centre word is read by its own thread and by the tile's threads
     // beside it; one of them stands for the others, of another
-    // synchronization group if there is one
+    // synchronization group if there is one (far)
     uint32_t other = HR_NO_THREAD;
     bool far = false;
-    if constexpr (CHECK) {
+    const auto reader = [&] {
         const uint32_t gm = 1023u >> e.wave_bits << e.wave_bits;
         const auto reads = [&](bool on, uint32_t u) {
             const bool f = ((t ^ u) & gm) != 0;
@@ -186,14 +186,15 @@ __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
         reads(tx < 15 && gx + 1 < nx, t + 1);
         reads(ty > 0, t - 16);
         reads(ty < 15 && gy + 1 < ny, t + 16);
-    }
+    };
     hr_by rows{0, 0, 0, 0}, cols{0, 0, 0, 0};
     if (inside) {
+        // a neighbour outside the grid reads the centre (no branches)
         const float c = tile[cl];
-        const float vn = gy > 0 ? tile[cl - TL] : c;
-        const float vs = gy + 1 < ny ? tile[cl + TL] : c;
-        const float vw = gx > 0 ? tile[cl - 1] : c;
-        const float ve = gx + 1 < nx ? tile[cl + 1] : c;
+        const float vn = tile[gy > 0 ? cl - TL : cl];
+        const float vs = tile[gy + 1 < ny ? cl + TL : cl];
+        const float vw = tile[gx > 0 ? cl - 1 : cl];
+        const float ve = tile[gx + 1 < nx ? cl + 1 : cl];
         if constexpr (CHECK) {
             if (e.count) {
                 hr_note_lds<0, CHECK>(e, th, lds_id, cl, HR_SITE_JACOBI_TILE);
@@ -202,8 +203,19 @@ __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
                 if (gx > 0) hr_note_lds<0, CHECK>(e, th, lds_id, cl - 1, HR_SITE_JACOBI_TILE);
                 if (gx + 1 < nx) hr_note_lds<0, CHECK>(e, th, lds_id, cl + 1, HR_SITE_JACOBI_TILE);
             }
-            if (!hr_own_lds_fast<0>(e, th, tsh, cl, other == HR_NO_THREAD ? 0u : far ? 2u : 1u))
-                late |= CENTRE;
+            // (whole waves of 4 rows: the rows above and below a wave's)
+            uint32_t others;
+            if (e.wave_bits == 6) {
+                const bool up = ty > 0, down = (ty < 15) & (gy + 1 < ny);
+                const bool beside = (tx > 0) | ((tx < 15) & (gx + 1 < nx));
+                others = (((ty & 3u) == 0) & up) | (((ty & 3u) == 3) & down) ? 2u
+                         : up | down | beside                               ? 1u
+                                                                             : 0u;
+            } else {
+                reader();
+                others = other == HR_NO_THREAD ? 0u : far ? 2u : 1u;
+            }
+            if (!hr_own_lds_fast<0>(e, th, tsh, cl, others)) late |= CENTRE;
             if ((hn || hs) && !hr_own_lds_fast<0>(e, th, tsh, lr, 0)) late |= ROW;
             if ((hw || he) && !hr_own_lds_fast<0>(e, th, tsh, lc, 0)) late |= COL;
         }
@@ -247,7 +259,10 @@ __device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
         if (late & OLD)
             hr_own<0>(e, hr_thread_of(e, lb, t), gold, xo, HR_SITE_JACOBI_CENTRE, by_row(),
                       by_col());
-        if (late & CENTRE) hr_own_lds<0>(e, th, tsh, lds_id, cl, HR_SITE_JACOBI_TILE, other);
+        if (late & CENTRE) {
+            reader();
+            hr_own_lds<0>(e, th, tsh, lds_id, cl, HR_SITE_JACOBI_TILE, other);
+        }
         if (late & ROW) hr_own_lds<0>(e, th, tsh, lds_id, lr, HR_SITE_JACOBI_TILE);
         if (late & COL) hr_own_lds<0>(e, th, tsh, lds_id, lc, HR_SITE_JACOBI_TILE);
         if (late & NEW) hr_own<1>(e, th, gnew, xn, HR_SITE_JACOBI_OUT, rows, cols);
