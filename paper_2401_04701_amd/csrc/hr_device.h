@@ -425,25 +425,24 @@ __device__ __noinline__ void hr_race8(hr_race_rec* ring, uint32_t* ctr, uint32_t
 // completed by this access is recorded; an exchange that overwrote updates
 // made since the load is folded back (and a race found by the fold is
 // recorded).  other / other_id: the wave-grouping partner lane, if any.
-template <int KIND>
-__device__ __forceinline__ void hr_settle(const hr_env& e, const hr_thread& t, uint64_t* sp,
-                                          uint32_t region, uint64_t index, uint32_t site,
-                                          uint64_t old, uint64_t nw, uint64_t r, uint32_t other,
-                                          uint64_t other_id)
+__device__ __forceinline__ void hr_settle(const hr_env& e, const hr_thread& t, uint32_t kind,
+                                          uint64_t* sp, uint32_t region, uint64_t index,
+                                          uint32_t site, uint64_t old, uint64_t nw, uint64_t r,
+                                          uint32_t other, uint64_t other_id)
 {
-    constexpr uint32_t k = KIND == 0 ? hr::CL_R : (KIND == 2 ? hr::CL_A : hr::CL_X);
+    const uint32_t k = hr::kind_class(kind);
     const uint64_t wm = hr::g::group_mask(e.wave_bits);
     if (nw == hr::T_RACE) {
         if (r != hr::T_RACE)
             hr_race8(e.ring, e.ctr, e.ring_cap, e.site_limit, e.launch_seq,
-                     ((uint32_t)KIND << 8) | ((site & 0xFFFFu) << 16), region, t.block, index,
-                     t.thread, t.gid, k, old, wm, other, other_id);
+                     (kind << 8) | ((site & 0xFFFFu) << 16), region, t.block, index, t.thread,
+                     t.gid, k, old, wm, other, other_id);
         return;
     }
     if (r != old) {
         const uint64_t before = hr_fold(sp, nw, r, wm);
         if (before != HR_NO_REPORT)
-            hr_ring_push(e, 0, region, t.block, index, t.thread, KIND, site, before, r,
+            hr_ring_push(e, 0, region, t.block, index, t.thread, kind, site, before, r,
                          HR_RACE_FOLD);
     }
 }
@@ -459,25 +458,29 @@ __device__ __forceinline__ uint64_t hr_step8(const uint16_t* tab, uint64_t old, 
     else return hr::g::step(old, id, k, wm);
 }
 
-template <int KIND, bool GROUP = false, bool PRE = false, bool LOG = false, bool TABLE = false>
-__device__ __forceinline__ void hr_check(const hr_env& e, const hr_thread& t, uint64_t* shadow,
-                                         uint64_t n, uint32_t region, uint64_t index,
-                                         uint64_t off, uint32_t site = 0, uint64_t pre = 0,
-                                         const uint16_t* tab = nullptr)
+//
+// hr_check_any takes the access kind at run time (the interpreter, whose
+// lanes mix kinds: one section for all of them instead of one after another);
+// lanes that wave grouping joins then agree in kind as well as in word.
+template <bool GROUP, bool PRE, bool LOG, bool TABLE>
+__device__ __forceinline__ void hr_check_any(const hr_env& e, const hr_thread& t, uint32_t kind,
+                                             uint64_t* shadow, uint64_t n, uint32_t region,
+                                             uint64_t index, uint64_t off, uint32_t site,
+                                             uint64_t pre, const uint16_t* tab)
 {
     if (t.enabled != 1 || !shadow) return;      // thread switched off / region not monitored
-    hr_count<LOG>(e, t, 0, region, index, KIND, site);
+    hr_count<LOG>(e, t, 0, region, index, kind, site);
     if (index >= n) {
         hr_set_flag(e, HR_DEVF_RANGE);
         return;
     }
-    constexpr uint32_t k = KIND == 0 ? hr::CL_R : (KIND == 2 ? hr::CL_A : hr::CL_X);
+    const uint32_t k = hr::kind_class(kind);
     uint64_t* sp = shadow + off;
     const uint64_t wm = hr::g::group_mask(e.wave_bits);
     uint32_t other = HR_NO_LANE;
     if (GROUP && e.group && e.wave_bits == 6) {     // lanes of one tile only when tiles are waves
         bool member;
-        other = hr_group((uint64_t)sp >> 3, e.group, &member);
+        other = hr_group((uint64_t)sp >> 3 | (uint64_t)kind << 60, e.group, &member);
         if (member) return;
     }
     const uint64_t old =
@@ -490,7 +493,16 @@ __device__ __forceinline__ void hr_check(const hr_env& e, const hr_thread& t, ui
     }
     if (nw == old) return;
     const uint64_t r = __hip_atomic_exchange(sp, nw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    hr_settle<KIND>(e, t, sp, region, index, site, old, nw, r, other, other_id);
+    hr_settle(e, t, kind, sp, region, index, site, old, nw, r, other, other_id);
+}
+
+template <int KIND, bool GROUP = false, bool PRE = false, bool LOG = false, bool TABLE = false>
+__device__ __forceinline__ void hr_check(const hr_env& e, const hr_thread& t, uint64_t* shadow,
+                                         uint64_t n, uint32_t region, uint64_t index,
+                                         uint64_t off, uint32_t site = 0, uint64_t pre = 0,
+                                         const uint16_t* tab = nullptr)
+{
+    hr_check_any<GROUP, PRE, LOG, TABLE>(e, t, KIND, shadow, n, region, index, off, site, pre, tab);
 }
 
 // A check split in two at a lane-affine site: hr_check_issue publishes the
@@ -534,7 +546,7 @@ __device__ __forceinline__ void hr_check_settle(const hr_env& e, const hr_thread
                                                 const hr_pend& p, uint32_t region, uint64_t index,
                                                 uint32_t site)
 {
-    if (p.sp) hr_settle<KIND>(e, t, p.sp, region, index, site, p.old, p.nw, p.r, HR_NO_LANE, 0);
+    if (p.sp) hr_settle(e, t, KIND, p.sp, region, index, site, p.old, p.nw, p.r, HR_NO_LANE, 0);
 }
 
 // The early load of hr_check<..., PRE = true>: the shadow word of element
@@ -598,50 +610,50 @@ __device__ __noinline__ void hr_race4(hr_race_rec* ring, uint32_t* ctr, uint32_t
                 before, with, 0);
 }
 
-template <int KIND>
-__device__ __forceinline__ void hr_settle4(const hr_env& e, const hr_thread& t, uint32_t* sp,
-                                           uint32_t region, uint64_t index, uint32_t site,
-                                           uint32_t old, uint32_t nw, uint32_t r, uint32_t other,
-                                           uint64_t other_id)
+__device__ __forceinline__ void hr_settle4(const hr_env& e, const hr_thread& t, uint32_t kind,
+                                           uint32_t* sp, uint32_t region, uint64_t index,
+                                           uint32_t site, uint32_t old, uint32_t nw, uint32_t r,
+                                           uint32_t other, uint64_t other_id)
 {
-    constexpr uint32_t k = KIND == 0 ? hr::CL_R : (KIND == 2 ? hr::CL_A : hr::CL_X);
+    const uint32_t k = hr::kind_class(kind);
     const uint64_t wm = hr::g::group_mask(e.wave_bits);
     const uint32_t lay = e.word4;
     if (nw == hr::T_RACE) {
         if (r != hr::T_RACE)
             hr_race4(e.ring, e.ctr, e.ring_cap, e.site_limit, e.launch_seq,
-                     0u | ((uint32_t)KIND << 8) | ((site & 0xFFFFu) << 16), region, t.block, index,
-                     t.thread, t.bc, t.wc, k, old, lay, wm, other, other_id);
+                     (kind << 8) | ((site & 0xFFFFu) << 16), region, t.block, index, t.thread,
+                     t.bc, t.wc, k, old, lay, wm, other, other_id);
         return;
     }
     if (r != old) {
         const uint32_t before = hr_fold4(sp, nw, r, wm, lay);
         if (before != HR_NO_REPORT4)
-            hr_ring_push(e, 0, region, t.block, index, t.thread, KIND, site,
+            hr_ring_push(e, 0, region, t.block, index, t.thread, kind, site,
                          hr::c::widen(before, lay), hr::c::widen(r, lay), HR_RACE_FOLD);
     }
 }
 
 // LAY: the word layout as a compile-time constant (0: the context's, e.word4).
-template <int KIND, bool GROUP = false, bool PRE = false, uint32_t LAY = 0, bool LOG = false>
-__device__ __forceinline__ void hr_check4(const hr_env& e, const hr_thread& t, uint32_t* shadow,
-                                          uint64_t n, uint32_t region, uint64_t index,
-                                          uint64_t off, uint32_t site = 0, uint32_t pre = 0)
+template <bool GROUP, bool PRE, uint32_t LAY, bool LOG>
+__device__ __forceinline__ void hr_check4_any(const hr_env& e, const hr_thread& t, uint32_t kind,
+                                              uint32_t* shadow, uint64_t n, uint32_t region,
+                                              uint64_t index, uint64_t off, uint32_t site,
+                                              uint32_t pre)
 {
     if (t.enabled != 1 || !shadow) return;
-    hr_count<LOG>(e, t, 0, region, index, KIND, site);
+    hr_count<LOG>(e, t, 0, region, index, kind, site);
     if (index >= n) {
         hr_set_flag(e, HR_DEVF_RANGE);
         return;
     }
-    constexpr uint32_t k = KIND == 0 ? hr::CL_R : (KIND == 2 ? hr::CL_A : hr::CL_X);
+    const uint32_t k = hr::kind_class(kind);
     uint32_t* sp = shadow + off;
     const uint32_t lay = LAY ? LAY : e.word4;
     const uint64_t wm = hr::g::group_mask(e.wave_bits);
     uint32_t other = HR_NO_LANE;
     if (GROUP && e.group && e.wave_bits == 6) {
         bool member;
-        other = hr_group((uint64_t)sp >> 2, e.group, &member);
+        other = hr_group((uint64_t)sp >> 2 | (uint64_t)kind << 62, e.group, &member);
         if (member) return;
     }
     const uint32_t wm4 = hr::c::group_mask(e.wave_bits, lay);
@@ -657,7 +669,15 @@ __device__ __forceinline__ void hr_check4(const hr_env& e, const hr_thread& t, u
     }
     if (nw == old) return;
     const uint32_t r = __hip_atomic_exchange(sp, nw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    hr_settle4<KIND>(e, t, sp, region, index, site, old, nw, r, other, other_id);
+    hr_settle4(e, t, kind, sp, region, index, site, old, nw, r, other, other_id);
+}
+
+template <int KIND, bool GROUP = false, bool PRE = false, uint32_t LAY = 0, bool LOG = false>
+__device__ __forceinline__ void hr_check4(const hr_env& e, const hr_thread& t, uint32_t* shadow,
+                                          uint64_t n, uint32_t region, uint64_t index,
+                                          uint64_t off, uint32_t site = 0, uint32_t pre = 0)
+{
+    hr_check4_any<GROUP, PRE, LAY, LOG>(e, t, KIND, shadow, n, region, index, off, site, pre);
 }
 
 struct hr_pend4 {
@@ -698,7 +718,7 @@ __device__ __forceinline__ void hr_check4_settle(const hr_env& e, const hr_threa
                                                  const hr_pend4& p, uint32_t region,
                                                  uint64_t index, uint32_t site)
 {
-    if (p.sp) hr_settle4<KIND>(e, t, p.sp, region, index, site, p.old, p.nw, p.r, HR_NO_LANE, 0);
+    if (p.sp) hr_settle4(e, t, KIND, p.sp, region, index, site, p.old, p.nw, p.r, HR_NO_LANE, 0);
 }
 
 __device__ __forceinline__ uint32_t hr_check4_load(const hr_thread& t, uint32_t* shadow,
@@ -732,18 +752,19 @@ __device__ __forceinline__ void hr_access(const hr_kargs& a, const hr_thread& t,
 // 4-byte shadow words live in LDS at `sh` (n_words of them, cleared to 0 at
 // block start).  LDS atomics are cheap, so this path keeps the
 // compare-and-swap loop.
-template <int KIND, bool LOG = false>
-__device__ __forceinline__ void hr_access_lds(const hr_env& e, const hr_thread& t, uint32_t* sh,
-                                              uint32_t n_words, uint32_t array_id, uint32_t index,
-                                              uint32_t site = 0)
+template <bool LOG = false>
+__device__ __forceinline__ void hr_access_lds_k(const hr_env& e, const hr_thread& t,
+                                                uint32_t kind, uint32_t* sh, uint32_t n_words,
+                                                uint32_t array_id, uint32_t index,
+                                                uint32_t site = 0)
 {
     if (t.enabled != 1) return;
-    hr_count<LOG>(e, t, 1, array_id, index, KIND, site);
+    hr_count<LOG>(e, t, 1, array_id, index, kind, site);
     if (index >= n_words) {
         hr_set_flag(e, HR_DEVF_RANGE);
         return;
     }
-    constexpr uint32_t k = KIND == 0 ? hr::CL_R : (KIND == 2 ? hr::CL_A : hr::CL_X);
+    const uint32_t k = hr::kind_class(kind);
     uint32_t* sp = sh + index;
     uint32_t old = __hip_atomic_load(sp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     for (;;) {
@@ -753,12 +774,20 @@ __device__ __forceinline__ void hr_access_lds(const hr_env& e, const hr_thread& 
         if (__hip_atomic_compare_exchange_strong(sp, &seen, nw, __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) {
             if (nw == hr::T_RACE)
-                hr_ring_push(e, 1, array_id, t.block, index, t.thread, KIND, site, old,
+                hr_ring_push(e, 1, array_id, t.block, index, t.thread, kind, site, old,
                              hr::l::step(hr::T_INIT, t.lid, k), 0);   // one access: split-free
             return;
         }
         old = seen;
     }
+}
+
+template <int KIND, bool LOG = false>
+__device__ __forceinline__ void hr_access_lds(const hr_env& e, const hr_thread& t, uint32_t* sh,
+                                              uint32_t n_words, uint32_t array_id, uint32_t index,
+                                              uint32_t site = 0)
+{
+    hr_access_lds_k<LOG>(e, t, KIND, sh, n_words, array_id, index, site);
 }
 
 // The LDS hooks of one reduction step of a thread: a read of word a, a read
@@ -821,37 +850,19 @@ __device__ __forceinline__ void hr_lds_rrw(const hr_env& e, const hr_thread& t, 
     }
 }
 
-// Runtime-kind forms (used where the kind is data, as in the interpreter).
+// A global check with the kind at run time, by the context's word size.
 template <bool LOG = false, bool TABLE = false>
 __device__ __forceinline__ void hr_check_k(const hr_env& e, const hr_thread& t, uint32_t kind,
                                            uint64_t* shadow, uint64_t n, uint32_t region,
                                            uint64_t index, uint64_t off, uint32_t site = 0,
                                            const uint16_t* tab = nullptr)
 {
-    if (e.word4) {
-        uint32_t* s4 = (uint32_t*)shadow;
-        if (kind == 0) hr_check4<0, true, false, 0, LOG>(e, t, s4, n, region, index, off, site);
-        else if (kind == 1) hr_check4<1, true, false, 0, LOG>(e, t, s4, n, region, index, off, site);
-        else hr_check4<2, true, false, 0, LOG>(e, t, s4, n, region, index, off, site);
-        return;
-    }
-    if (kind == 0)
-        hr_check<0, true, false, LOG, TABLE>(e, t, shadow, n, region, index, off, site, 0, tab);
-    else if (kind == 1)
-        hr_check<1, true, false, LOG, TABLE>(e, t, shadow, n, region, index, off, site, 0, tab);
+    if (e.word4)
+        hr_check4_any<true, false, 0, LOG>(e, t, kind, (uint32_t*)shadow, n, region, index, off,
+                                           site, 0);
     else
-        hr_check<2, true, false, LOG, TABLE>(e, t, shadow, n, region, index, off, site, 0, tab);
-}
-
-template <bool LOG = false>
-__device__ __forceinline__ void hr_access_lds_k(const hr_env& e, const hr_thread& t,
-                                                uint32_t kind, uint32_t* sh, uint32_t n_words,
-                                                uint32_t array_id, uint32_t index,
-                                                uint32_t site = 0)
-{
-    if (kind == 0) hr_access_lds<0, LOG>(e, t, sh, n_words, array_id, index, site);
-    else if (kind == 1) hr_access_lds<1, LOG>(e, t, sh, n_words, array_id, index, site);
-    else hr_access_lds<2, LOG>(e, t, sh, n_words, array_id, index, site);
+        hr_check_any<true, false, LOG, TABLE>(e, t, kind, shadow, n, region, index, off, site, 0,
+                                              tab);
 }
 
 __device__ __forceinline__ void hr_retag(const hr_env& e, hr_thread& t)

@@ -165,8 +165,10 @@ __global__ __launch_bounds__(1024) void k_program(hr_kargs a, prog_map pm, uint3
         }
         if (k0 < 0) k0 = 0;
         if (k1 > (int64_t)n_ops) k1 = (int64_t)n_ops;
+        uint32_t op_next = k0 < k1 ? ops[k0] : 0u;
         for (int64_t k = k0; k < k1; ++k) {
-            const uint32_t op = ops[k];
+            const uint32_t op = op_next;        // the next one is loaded meanwhile
+            if (k + 1 < k1) op_next = ops[k + 1];
             const uint32_t idx = op & 0xFFFFFFu, reg = (op >> 24) & 7u, kind = (op >> 27) & 3u;
             if (kind == 3) {                        // switch this thread's checking
                 hr_thread_enable(th, idx & 1u);
