@@ -22,7 +22,7 @@
 // out[lb*T + t].  When n < 2T a thread's step-0 operand was loaded by
 // another thread, so a barrier also follows the loads.
 template <int CHECK, class G = hr_gref>
-__device__ void reduce_body(const hr_env& e, const G& gin, const G& gout,
+__device__ __forceinline__ void reduce_body(const hr_env& e, const G& gin, const G& gout,
                             const int32_t* __restrict__ in, int32_t* __restrict__ out, uint32_t n,
                             uint32_t T, uint32_t lb, uint32_t t, int32_t drop, int32_t* s,
                             uint32_t* sh, uint32_t lds_id)
@@ -331,7 +331,7 @@ constexpr uint32_t labelprop_lds_words(uint32_t vt) { return 3 * vt + 4; }
 // checked, the column index of edge k+2, and the seeded flag of edge k+1 and
 // the shadow word of its target, are already in flight.
 template <int CHECK, class G = hr_gref, bool COH = false>
-__device__ void labelprop_body(const hr_env& e, const G& glab, const G& grp, const G& gcol,
+__device__ __forceinline__ void labelprop_body(const hr_env& e, const G& glab, const G& grp, const G& gcol,
                                int32_t* __restrict__ label, const int32_t* __restrict__ rp,
                                const int32_t* __restrict__ col, const uint8_t* __restrict__ mask,
                                uint32_t n, uint32_t T, uint32_t lb, uint32_t t)

@@ -85,7 +85,7 @@ struct hr_tile_sync {
 // and not at its end, took 0.184 ms, issue-bound; plain, nontemporal or
 // coherent loads and stores of the words made no difference.
 template <int CHECK, class G = hr_gref, class SYNC = hr_block_sync, bool COH = false>
-__device__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
+__device__ __forceinline__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
                             const float* __restrict__ uo, float* __restrict__ un, uint32_t ny,
                             uint32_t nx, uint32_t nbx, const int32_t* __restrict__ seeds,
                             uint32_t lb, uint32_t t, float* tile, uint32_t* tsh, uint32_t lds_id,
