@@ -76,7 +76,7 @@ struct hr_tile_sync {
 // COH: the cells are read and written past the caches (agent scope), for a
 // kernel whose blocks run several sweeps with only a counter between them.
 //
-// What bounds it: memory.  4096 x 4096: 0.143 ms per launch, 4.7 TB/s of the
+// What bounds it: memory.  4096 x 4096: 0.136 ms per launch, 4.9 TB/s of the
 // 671 MB of grids and shadow words (a large copy reaches 4.9 TB/s here),
 // against 0.278 ms with every access published by its own thread's exchange
 // (100 memory-side requests per tile, which run at 25 G/s on the chip, and
@@ -271,6 +271,18 @@ __device__ __forceinline__ void jacobi_body(const hr_env& e, const G& gold, cons
 
 namespace {
 
+// The tile of a hardware block.  Blocks go to the chip's eight dies in turn,
+// each with its own L2; of 256 consecutive tiles a die takes 32 consecutive
+// ones, so that neighbours share the lines of their halos and of the data rows
+// (a tile's row is half a 128-byte line) in one L2.  4096 x 4096: 0.145 to
+// 0.136 ms per launch (0.141 with 2, 0.139 with 8 at a time); with 4-byte words
+// 0.066 to 0.063 ms at 2048 x 3072, the clear with it.
+__device__ __forceinline__ uint32_t jacobi_tile()
+{
+    const uint32_t b = blockIdx.y * gridDim.x + blockIdx.x, n = gridDim.x * gridDim.y;
+    return b < (n & ~255u) ? (b & ~255u) | (b & 7u) << 5 | ((b >> 3) & 31u) : b;
+}
+
 // One 16 x 16 tile per hardware block, on row-major shadow maps (CHECK 0:
 // plain, 1: checked).  8 waves per SIMD: the hook's scalar registers would
 // otherwise cap the occupancy at 7.
@@ -283,9 +295,8 @@ __global__ __launch_bounds__(256, 8) void k_jacobi(hr_kargs a, hr_gref gold, hr_
     __shared__ float tile[JACOBI_TILE_WORDS];
     __shared__ uint32_t tsh[CHECK ? JACOBI_TILE_WORDS : 1];
     using G = hr_gref_map<0, 0>;
-    const uint32_t lb = blockIdx.y * gridDim.x + blockIdx.x;
-    jacobi_body<CHECK, G>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, gridDim.x, seeds,
-                                lb, threadIdx.x, tile, tsh, 0);
+    jacobi_body<CHECK, G>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, gridDim.x, seeds, jacobi_tile(),
+                          threadIdx.x, tile, tsh, 0);
 }
 
 // Four consecutive tiles per 1024-thread block, each quarter of the block
@@ -351,8 +362,7 @@ __global__ __launch_bounds__(256, 8) void k_jacobi_tab(hr_kargs a, hr_gref gold,
         t = reinterpret_cast<const uint16_t*>(stab);
     }
     jacobi_body<CHECK, G>(a.env, G{hr_gref_tab{gold, t}}, G{hr_gref_tab{gnew, t}}, uo, un,
-                                ny, nx, gridDim.x, seeds, blockIdx.y * gridDim.x + blockIdx.x,
-                                threadIdx.x, tile, tsh, 0);
+                                ny, nx, gridDim.x, seeds, jacobi_tile(), threadIdx.x, tile, tsh, 0);
 }
 
 // The checked sweep on tiled shadow maps: both grids tiled by 2^TW x 2^TH
@@ -369,7 +379,7 @@ __global__ __launch_bounds__(256, 8) void k_jacobi_tiled(hr_kargs a, hr_gref gol
     __shared__ uint32_t tsh[JACOBI_TILE_WORDS];
     using G = hr_gref_map<TW, TH>;
     jacobi_body<CHECK, G>(a.env, G{gold}, G{gnew}, uo, un, ny, nx, gridDim.x, seeds,
-                               blockIdx.y * gridDim.x + blockIdx.x, threadIdx.x, tile, tsh, 0);
+                               jacobi_tile(), threadIdx.x, tile, tsh, 0);
 }
 
 // The checked sweep on 4-byte shadow words, with the word layout as a
@@ -386,7 +396,7 @@ __global__ __launch_bounds__(256, LAY ? 8 : 7) void k_jacobi4(hr_kargs a, hr_gre
     __shared__ float tile[JACOBI_TILE_WORDS];
     __shared__ uint32_t tsh[JACOBI_TILE_WORDS];
     jacobi_body<CHECK, hr_gref4t<LAY>>(a.env, gold, gnew, uo, un, ny, nx, gridDim.x, seeds,
-                                            blockIdx.y * gridDim.x + blockIdx.x, threadIdx.x,
+                                            jacobi_tile(), threadIdx.x,
                                             tile, tsh, 0);
 }
 

@@ -138,3 +138,34 @@ def test_epoch_shared_with_another_kernel(env, region, first, where, word4):
             ctx.reset()
             g.replay()
             assert keys_of(ctx, regs) == want
+
+
+@pytest.mark.parametrize("word4", [False, True])
+@pytest.mark.parametrize("ny,nx", [(16, 4095), (17, 4096), (16 * 15, 16 * 17 + 1), (270, 300)])
+def test_tiles_over_the_dies(env, ny, nx, word4):
+    """Grids of 255, 256, 512 and other counts of tiles: the blocks' order over
+    the chip's dies covers every tile once."""
+    torch, hr = env
+    say("tiles over dies", ny, nx, "word4", word4)
+    seeds = si.jacobi_seeds(ny, nx, 8, count=40)
+    tab = torch.from_numpy(si.jacobi_seed_table(ny, nx, seeds)).cuda()
+    u = [torch.from_numpy(si.jacobi_grid(ny, nx, 3)).cuda(),
+         torch.zeros((ny, nx), device="cuda")]
+    first = u[0].clone()
+    with hr.Context(word4=word4, count_checks=True) as ctx:
+        regs = [ctx.shadow_alloc(x) for x in u]
+        ctx.jacobi_check(regs[0], regs[1], u[0], u[1], None)
+        ctx.kernel_end()
+        assert ctx.flagged() == set()
+        want = torch.zeros_like(first)
+        hr.jacobi_plain(first, want, None)
+        assert torch.equal(u[1], want)
+        x = first.double()
+        n, s = torch.cat([x[:1], x[:-1]]), torch.cat([x[1:], x[-1:]])
+        w, e = torch.cat([x[:, :1], x[:, :-1]], 1), torch.cat([x[:, 1:], x[:, -1:]], 1)
+        assert (want.double() - 0.2 * (x + n + s + w + e)).abs().max() < 1e-6
+        ctx.jacobi_check(regs[0], regs[1], u[0], u[1], tab)
+        ctx.kernel_end()
+        got, st = keys_of(ctx, regs), ctx.status
+    assert st == 0 and got == {(0, 1, 0, k[3]) for k in oracle.flagged(
+        oracle.model_jacobi(ny, nx, 1, tab.cpu().numpy()))}
