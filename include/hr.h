@@ -4,8 +4,8 @@
  * The checker follows HiRace (Jacobson, Burtscher, Gopalakrishnan): every
  * monitored 4-byte element of global memory or LDS has a constant-size
  * shadow word holding a per-location state machine; each instrumented access
- * advances it with a compare-and-swap (paper Sec. IV-B, Algorithm 1), and a
- * transition into the race state is appended once to a report ring
+ * advances it atomically (paper Sec. IV-B, Algorithm 1), and a transition
+ * into the race state is appended once to a report ring
  * (Sec. V-C reports races on unique addresses).  Races are the paper's
  * (Sec. II-A): same location, different threads, at least one write (or a
  * plain access meeting an atomic, Sec. III-B), not ordered by a launch

@@ -217,15 +217,16 @@ __device__ __forceinline__ lp_share lp_share_of(const lp_part* part, const int32
     return s;
 }
 
-// What bounds it: random requests past the L2, a label and a shadow word per
-// edge, and in smaller graphs the hubs' words: until the first update of a
+// What bounds it: whole lines read for one label or one shadow word of an
+// edge's target (2^25 edges: 3.3 GB per launch, 4.5 times the words that the
+// sweep needs, at 4.3 TB/s), and in smaller graphs the hubs' words: until the first update of a
 // hub's word lands, every lane with an edge into the hub exchanges the word,
 // and exchanges of one word run one after another.  So in the blocks that
 // start the launch (sh.pilot) one wave's edges go first, and the others find
 // the hubs' words settled.  Per checked launch, R-MAT: 100,003 vertices and
 // 800,024 edges, CSR monitored, 0.070 ms (0.16 without the first wave's
-// start, 0.26 cut by vertices); 2^22 vertices and 2^25 edges 0.73 ms (3.2 cut
-// by vertices).  One edge per lane at a time, in 64
+// start, 0.26 cut by vertices); 2^22 vertices and 2^25 edges 0.64 to 0.76 ms
+// (3.2 cut by vertices).  One edge per lane at a time, in 64
 // registers (two 1024-thread blocks per compute unit), was as fast as 2 or 4
 // edges per lane (with more registers) and as loading the next edge's words
 // ahead.  vt: vertices loaded at a time.

@@ -410,11 +410,12 @@ __device__ __noinline__ void hr_race8(hr_race_rec* ring, uint32_t* ctr, uint32_t
 //
 // The copy-compute-publish loop of the paper's Algorithm 1, published with an
 // atomic exchange instead of a compare-and-swap (on gfx950 a 64-bit exchange
-// costs less than half a 64-bit compare-and-swap).  The coherent load decides
-// the transition; an unchanged word costs nothing more.  If the exchange
-// returns the loaded word, it acted exactly as a successful compare-and-swap.
-// Otherwise it overwrote updates made since the load, and hr_fold merges
-// them back.
+// costs less than half a 64-bit compare-and-swap).  The loaded word decides
+// the transition; it comes through the caches and may be stale (where the
+// load is issued, below, says why that is sound).  An unchanged word costs
+// nothing more.  If the exchange returns the loaded word, it acted exactly as
+// a successful compare-and-swap.  Otherwise it overwrote updates that the
+// load did not see, and hr_fold merges them back.
 //
 // PRE: the caller loaded the word earlier (hr_check_load) and passes it as
 // `pre`, to overlap that load with its other work.  Between the load and
@@ -458,8 +459,7 @@ __device__ __forceinline__ uint64_t hr_step8(const uint16_t* tab, uint64_t old, 
     else return hr::g::step(old, id, k, wm);
 }
 
-//
-// hr_check_any takes the access kind at run time (the interpreter, whose
+// The check itself, with the access kind at run time (the interpreter, whose
 // lanes mix kinds: one section for all of them instead of one after another);
 // lanes that wave grouping joins then agree in kind as well as in word.
 template <bool GROUP, bool PRE, bool LOG, bool TABLE>

@@ -76,9 +76,9 @@ struct hr_tile_sync {
 // COH: the cells are read and written past the caches (agent scope), for a
 // kernel whose blocks run several sweeps with only a counter between them.
 //
-// What bounds it: memory.  4096 x 4096: 0.136 ms per launch, 4.9 TB/s of the
-// 671 MB of grids and shadow words (a large copy reaches 4.9 TB/s here),
-// against 0.278 ms with every access published by its own thread's exchange
+// What bounds it: memory.  4096 x 4096: 0.129 ms per launch, 5.2 TB/s of the
+// 671 MB of grids and shadow words (a large copy reaches 4.9 to 5.8 TB/s
+// here), against 0.278 ms with every access published by its own thread's exchange
 // (100 memory-side requests per tile, which run at 25 G/s on the chip, and
 // 530 vector instructions per wave).  The general transitions in place of
 // the closed forms (hr_own_fast), with their rare paths inside the kernel
@@ -275,8 +275,8 @@ namespace {
 // each with its own L2; of 256 consecutive tiles a die takes 32 consecutive
 // ones, so that neighbours share the lines of their halos and of the data rows
 // (a tile's row is half a 128-byte line) in one L2.  4096 x 4096: 0.145 to
-// 0.136 ms per launch (0.141 with 2, 0.139 with 8 at a time); with 4-byte words
-// 0.066 to 0.063 ms at 2048 x 3072, the clear with it.
+// 0.136 ms per launch, each timed on its own (0.141 with 2, 0.139 with 8 at a
+// time); with 4-byte words 0.066 to 0.063 ms at 2048 x 3072, the clear with it.
 __device__ __forceinline__ uint32_t jacobi_tile()
 {
     const uint32_t b = blockIdx.y * gridDim.x + blockIdx.x, n = gridDim.x * gridDim.y;
