@@ -81,8 +81,9 @@ struct hr_ctx_s {
     bool epoch_used = false, epoch_shared = false, epoch_excl = false;
     hipStream_t epoch_stream = nullptr;
     // Room for the pieces of a label-propagation launch (after the debug
-    // counters, in their allocation) and the stream that used it last.
-    bool lp_used = false;
+    // counters, in their allocation): whether a launch ever used it, whether
+    // one did since the job started, and the stream of the last.
+    bool lp_any = false, lp_used = false;
     hipStream_t lp_stream = nullptr;
     hr_host_buf h_ring, h_keys;      // hr_report's copy of the ring and its sort
 };
@@ -91,9 +92,10 @@ struct hr_ctx_s {
 // (may be NULL: the kernel does not use it) receives the launch's env.excl:
 // every checked launch of the epoch so far was made on `s`, so none runs
 // beside it, and a later one will not either, since a launch on another
-// stream (or hr_dev_args) first waits here for the exclusive ones.  Not
-// granted while `s` is being captured (a graph may be launched anywhere),
-// nor on the per-thread stream, whose handle names several streams.
+// stream (or hr_dev_args) first waits here for the exclusive ones.  Neither
+// while `s` is being captured (a graph may be launched anywhere) nor on the
+// per-thread stream, whose handle names several streams: such a launch, too,
+// waits for the exclusive ones, and none after it in the epoch is.
 hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl);
 
 // Bytes of the counter words at the start of a context's counter-and-ring
@@ -112,8 +114,9 @@ hr_env hr_env_of(const hr_config& cfg, hr_race_rec* ring, uint32_t* ctr,
 hr_env hr_make_env(hr_ctx c);
 void hr_fill_args(hr_ctx c, hr_kargs* a);
 // The context's room for the pieces of a label-propagation launch on `s`, or
-// NULL: a launch on another stream may still use it, or `s` is being captured
-// or names several streams (see hr_epoch_enter).
+// NULL: a launch of this job on another stream may still use it, or `s` is
+// being captured or names several streams (see hr_epoch_enter).  A job's first
+// launch on another stream than the last job's waits for all launched work.
 lp_part* hr_lp_room(hr_ctx c, hipStream_t s);
 // Bytes of that room.
 constexpr size_t HR_LP_ROOM_BYTES = (HR_LP_PIECES + 1) * 8;

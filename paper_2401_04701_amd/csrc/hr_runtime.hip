@@ -298,13 +298,36 @@ void hr_fill_args(hr_ctx c, hr_kargs* a)
     }
 }
 
-// Wait for the exclusive launches of the epoch; from here on it is shared.
+// Wait for a stream's work, also while another stream records a graph; a stream
+// that records one itself is not waited for (hipErrorStreamCaptureUnsupported).
+// If its owner has destroyed the stream, wait for the device.
+static hipError_t wait_for(hipStream_t s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return hipDeviceSynchronize();
+    }
+    if (cap != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    hipError_t err = hipThreadExchangeStreamCaptureMode(&mode);
+    if (err != hipSuccess) return err;
+    err = hipStreamSynchronize(s);
+    const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
+    return err != hipSuccess ? err : back;
+}
+
+// Wait for the exclusive launches of the epoch; from here on it is shared.  On
+// a stream that has begun to record a graph since, its earlier launches cannot
+// be waited for: the graph's come after them wherever it is replayed in their
+// order.
 static hr_status epoch_share(hr_ctx c)
 {
     c->epoch_shared = true;
     if (!c->epoch_excl) return HR_OK;
     c->epoch_excl = false;
-    return hipStreamSynchronize(c->epoch_stream) == hipSuccess ? HR_OK : HR_E_HIP;
+    const hipError_t err = wait_for(c->epoch_stream);
+    return err == hipSuccess || err == hipErrorStreamCaptureUnsupported ? HR_OK : HR_E_HIP;
 }
 
 static void epoch_begin(hr_ctx c)
@@ -322,14 +345,14 @@ static bool one_eager_stream(hipStream_t s)
 
 hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
 {
-    if (c->epoch_used && c->epoch_stream != s) {
-        const hr_status st = epoch_share(c);
+    if (!one_eager_stream(s) || (c->epoch_used && c->epoch_stream != s)) {
+        const hr_status st = epoch_share(c);    // a graph may be replayed on any stream
         if (st != HR_OK) return st;
     }
     c->epoch_used = true;
     c->epoch_stream = s;
     if (!excl) return HR_OK;
-    *excl = !c->epoch_shared && one_eager_stream(s);
+    *excl = !c->epoch_shared;
     c->epoch_excl |= *excl != 0;
     return HR_OK;
 }
@@ -337,11 +360,10 @@ hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
 lp_part* hr_lp_room(hr_ctx c, hipStream_t s)
 {
     if (!one_eager_stream(s)) return nullptr;
-    if (c->lp_used && c->lp_stream != s && hipStreamQuery(c->lp_stream) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
+    if (c->lp_any && c->lp_stream != s) {
+        if (c->lp_used || wait_for(c->lp_stream) != hipSuccess) return nullptr;
     }
-    c->lp_used = true;
+    c->lp_any = c->lp_used = true;
     c->lp_stream = s;
     return (lp_part*)(c->count + HR_COUNT_SLOTS);
 }
@@ -648,6 +670,7 @@ extern "C" hr_status hr_reset(hr_ctx c, void* stream)
     c->launch_seq = 0;
     c->carried.clear();
     epoch_begin(c);
+    c->lp_used = false;
     return HR_OK;
 }
 

@@ -164,3 +164,28 @@ def test_two_streams_and_capture(capture):
             assert ctx.flagged() == set()
     for (rp, col), x in zip(graphs, labels):
         assert (x.cpu().numpy() == fixed_point(rp, col)).all()
+
+
+def test_jobs_on_alternating_streams():
+    """One context's jobs on two streams in turn, each job its own graph."""
+    import torch
+    from paper_2401_04701_amd import hr
+    print("[case] pieces alternating streams", flush=True)
+    graphs = [graph("two_hubs"), graph("first_hub")]
+    up = lambda a: torch.from_numpy(a).cuda()
+    dev = [[up(a) for a in (*g, np.zeros(g[1].shape[0], np.uint8))] for g in graphs]
+    labels = [torch.arange(g[0].shape[0] - 1, dtype=torch.int32, device="cuda") for g in graphs]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    with hr.Context() as ctx:
+        regs = [ctx.shadow_alloc(x) for x in labels]
+        torch.cuda.synchronize()
+        for job in range(8):
+            i = job % 2
+            with torch.cuda.stream(streams[i]):
+                ctx.reset()
+                for _ in range(10):
+                    ctx.labelprop_check(regs[i], labels[i], *dev[i])
+                    ctx.kernel_end()
+                assert ctx.flagged() == set()
+    for (rp, col), x in zip(graphs, labels):
+        assert (x.cpu().numpy() == fixed_point(rp, col)).all()

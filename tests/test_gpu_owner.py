@@ -140,6 +140,51 @@ def test_epoch_shared_with_another_kernel(env, region, first, where, word4):
             assert keys_of(ctx, regs) == want
 
 
+@pytest.mark.parametrize("recorded", ["sweep", "writes"])
+@pytest.mark.parametrize("order", ["eager first", "graph first"])
+@pytest.mark.parametrize("where", ["same", "other"])
+def test_epoch_shared_with_a_graph(env, where, order, recorded):
+    """One epoch's sweep and writes, one launched and one recorded (on the same
+    stream or another one) and then replayed on a third, whichever is first."""
+    torch, hr = env
+    ny, nx = 33, 40
+    cells = list(range(0, ny * nx, 7))
+    launch = writes_by(9, cells, 1)
+    say("epoch and graph", where, order, recorded)
+    u = [torch.from_numpy(si.jacobi_grid(ny, nx, 3)).cuda(),
+         torch.zeros((ny, nx), device="cuda")]
+    prog = hr.DeviceProgram(launch)
+    want = oracle.flagged(np.concatenate([oracle.model_jacobi(ny, nx, 1, None),
+                                          oracle.model_launch(launch, 0)]))
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    with hr.Context() as ctx:
+        regs = [ctx.shadow_alloc(x) for x in u]
+        calls = [lambda: ctx.jacobi_check(regs[0], regs[1], u[0], u[1], None),
+                 lambda: ctx.program_check(prog, regs, 0)]
+        if recorded == "sweep":
+            calls.reverse()
+        eager, graph = calls
+        torch.cuda.synchronize()
+
+        def launch_eager():
+            with torch.cuda.stream(streams[0]):
+                eager()
+
+        g = torch.cuda.CUDAGraph()
+        if order == "eager first":
+            launch_eager()
+        with torch.cuda.graph(g, stream=streams[0 if where == "same" else 1]):
+            graph()
+        if order == "graph first":
+            launch_eager()
+        for _ in range(3):
+            with torch.cuda.stream(streams[2]):
+                g.replay()
+        torch.cuda.synchronize()
+        ctx.kernel_end()
+        assert keys_of(ctx, regs) == want
+
+
 @pytest.mark.parametrize("word4", [False, True])
 @pytest.mark.parametrize("ny,nx", [(16, 4095), (17, 4096), (16 * 15, 16 * 17 + 1), (270, 300)])
 def test_tiles_over_the_dies(env, ny, nx, word4):
