@@ -406,6 +406,7 @@ class Context:
                       wave_bits, thread_bits, coalesce_width, log_capacity, 0)
         self.wave_bits = wave_bits or 6
         self._cap = _report_cap(ring_capacity)
+        self._spare = []               # a report's unused room, for the next one
         self._c = ctypes.c_void_p(0)
         self._stream = _stream_ptr(stream)
         _check("hr_ctx_create", _lib.hr_ctx_create(ctypes.byref(self._c), ctypes.byref(cfg),
@@ -469,15 +470,26 @@ class Context:
         n = ctypes.c_size_t(0)
         cap = self._cap
         while True:
-            out = np.empty(cap, dtype=RACE_DTYPE)
-            st = _lib.hr_report(self._c, out.ctypes.data_as(ctypes.c_void_p), cap,
+            # Room for the whole ring, kept while reports are small: freeing
+            # that much makes the allocator serve the caller's next arrays of
+            # up to that size from its heap, where np.zeros writes them.
+            try:
+                out = self._spare.pop()
+            except IndexError:
+                out = np.empty(cap, dtype=RACE_DTYPE)
+            if len(out) < cap:
+                out = np.empty(cap, dtype=RACE_DTYPE)
+            st = _lib.hr_report(self._c, out.ctypes.data_as(ctypes.c_void_p), len(out),
                                 ctypes.byref(n), _stream_ptr(stream))
-            if st == HR_E_INVAL and n.value > cap:
+            if st == HR_E_INVAL and n.value > len(out):
                 cap = int(n.value)
                 continue
             _check("hr_report", st)
             self.status = st
-            return out[:n.value], st
+            if n.value > 4096:
+                return out[:n.value], st
+            self._spare[:] = [out]
+            return out[:n.value].copy(), st
 
     def flagged(self, stream=None) -> set:
         return _races_to_keys(self.report(stream)[0])

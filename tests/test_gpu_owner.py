@@ -214,3 +214,24 @@ def test_tiles_over_the_dies(env, ny, nx, word4):
         got, st = keys_of(ctx, regs), ctx.status
     assert st == 0 and got == {(0, 1, 0, k[3]) for k in oracle.flagged(
         oracle.model_jacobi(ny, nx, 1, tab.cpu().numpy()))}
+
+
+@pytest.mark.parametrize("side", [33, 1100])       # below and above 4,096 records
+def test_reports_do_not_share_memory(env, side):
+    """A report's records stay as they were when the next report is made."""
+    torch, hr = env
+    say("two reports", side)
+    tab = torch.from_numpy(full_table(side, side)).cuda()
+    u = [torch.from_numpy(si.jacobi_grid(side, side, 3)).cuda(),
+         torch.zeros((side, side), device="cuda")]
+    with hr.Context() as ctx:
+        regs = [ctx.shadow_alloc(x) for x in u]
+        ctx.jacobi_check(regs[0], regs[1], u[0], u[1], tab)
+        ctx.kernel_end()
+        first = ctx.report()[0]
+        kept = first.copy()
+        assert (len(first) > 4096) == (side > 1000)
+        ctx.reset()
+        assert len(ctx.report()[0]) == 0
+        again = ctx.report()[0]
+        assert len(again) == 0 and (first == kept).all()
