@@ -73,9 +73,13 @@ __global__ __launch_bounds__(256) void k_batch_cut(const hr_inst_dev* __restrict
 // live in scratch).  The autotuner picks between them by measurement.
 //
 // Thread 0 alone claims items, waits for phases and counts finished items.
-// Each of those thread-0 regions sits strictly between two block barriers,
-// and every iteration ends with a barrier, so no divergent region spans the
-// loop's back edge and every barrier runs with the whole block active.
+// Each of those thread-0 regions ends at a block barrier, and no divergent
+// region spans the loop's back edge, so every barrier runs with the whole
+// block active.  What thread 0 tells the others it writes before a barrier
+// and they read after it; a word is written again only after a further
+// barrier (tests/test_batch_worker.py).  So the count that ends an item has a
+// word of its own: no barrier lies between its reads and the next item's
+// s_go.
 template <int MIN_WAVES>
 __device__ __forceinline__ void batch_loop(const hr_env& base, const hr_inst_dev* __restrict__ insts,
                                            const uint64_t* __restrict__ items, uint32_t n_items,
@@ -83,7 +87,7 @@ __device__ __forceinline__ void batch_loop(const hr_env& base, const hr_inst_dev
 {
     extern __shared__ uint32_t smem[];
     __shared__ uint64_t s_item;
-    __shared__ uint32_t s_go;
+    __shared__ uint32_t s_go, s_ended;
     if (threadIdx.x == 0) s_item = claim(cursor, items, n_items);
     __syncthreads();
     for (;;) {
@@ -121,11 +125,11 @@ __device__ __forceinline__ void batch_loop(const hr_env& base, const hr_inst_dev
         __syncthreads();                                // every hook of the item is done
         uint32_t* const d = done + I.done_off + phase;
         if (threadIdx.x == 0) {
-            s_go = __hip_atomic_fetch_add(d, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s_ended = __hip_atomic_fetch_add(d, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_item = claim(cursor, items, n_items);
         }
         __syncthreads();
-        if (renews(I) && uni(s_go) + 1 == I.items) {
+        if (renews(I) && uni(s_ended) + 1 == I.items) {
             // the phase's last item: the labels that the next phase's pieces
             // continue with (it waits for one count more)
             for (uint32_t i = threadIdx.x; i <= I.items; i += blockDim.x) {
