@@ -131,19 +131,22 @@ __device__ __forceinline__ void lp_set(int32_t* p, int32_t v)
 }
 
 // Where piece i of a job begins: its first vertex v, its first edge
-// i * length - v, and, when that edge belongs to vertex v - 1, that vertex's
-// label.
+// row_ptr[0] + i * length - v, and, when that edge belongs to vertex v - 1,
+// that vertex's label.
 struct lp_part {
     uint32_t v;
     int32_t label;
 };
 
-// Length of a piece when n vertices and row_ptr[n] edges are cut into
-// `pieces`, and the first position of piece i.
-__device__ __forceinline__ uint64_t lp_edges(const int32_t* __restrict__ rp, uint32_t n)
+// Vertex v's edges are row_ptr[v] .. row_ptr[v + 1]; in a range of a larger
+// graph's rows row_ptr[0] is not 0.  lp_edge: the edges before vertex v's.
+__device__ __forceinline__ uint64_t lp_edge(const int32_t* __restrict__ rp, uint64_t v)
 {
-    return (uint64_t)max(rp[n], 0);
+    return (uint64_t)max((int64_t)rp[v] - rp[0], (int64_t)0);
 }
+
+// The first position of piece i when n vertices and `edges` edges are cut
+// into `pieces` of one length.
 __device__ __forceinline__ uint64_t lp_begin(uint64_t edges, uint32_t n, uint32_t pieces,
                                              uint32_t i)
 {
@@ -152,19 +155,19 @@ __device__ __forceinline__ uint64_t lp_begin(uint64_t edges, uint32_t n, uint32_
 }
 
 // Find the begin of piece i (i <= pieces), one wave.  Vertex v lies at
-// position v + row_ptr[v]: the piece's first vertex is the first one at or
+// position v + lp_edge(v): the piece's first vertex is the first one at or
 // past the piece's begin, found by 64 probes a round.
 __device__ __forceinline__ void lp_cut(lp_part* __restrict__ part, const int32_t* label,
                                        const int32_t* __restrict__ rp, uint32_t n,
                                        uint32_t pieces, uint32_t i)
 {
     const uint32_t lane = __lane_id();
-    const uint64_t at = lp_begin(lp_edges(rp, n), n, pieces, i);
+    const uint64_t at = lp_begin(lp_edge(rp, n), n, pieces, i);
     uint32_t lo = 0, hi = n;               // the answer is in lo..hi
     while (lo < hi) {
         const uint32_t m = hi - lo, step = (m + 63u) / 64u;
         const uint64_t q = (uint64_t)lo + (uint64_t)lane * step + step - 1;
-        const uint64_t hit = __ballot(q < hi && q + (uint64_t)max(rp[q < hi ? q : lo], 0) >= at);
+        const uint64_t hit = __ballot(q < hi && q + lp_edge(rp, q < hi ? q : lo) >= at);
         if (hit == 0) {
             lo += m / step * step;
         } else {
@@ -174,7 +177,7 @@ __device__ __forceinline__ void lp_cut(lp_part* __restrict__ part, const int32_t
         }
     }
     if (lane == 0) {
-        const bool cont = lo > 0 && at - lo < (uint64_t)max(rp[lo], 0);
+        const bool cont = lo > 0 && at - lo < lp_edge(rp, lo);
         part[i].v = lo;
         part[i].label = cont ? __hip_atomic_load(label + (lo - 1), __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT)
@@ -197,7 +200,8 @@ struct lp_share {
 __device__ __forceinline__ lp_share lp_share_of(const lp_part* part, const int32_t* __restrict__ rp,
                                                 uint32_t n, uint32_t pieces, uint32_t i)
 {
-    const uint64_t edges = lp_edges(rp, n);
+    const uint64_t edges = lp_edge(rp, n);
+    const uint32_t first = (uint32_t)rp[0];
     const auto load = [&](uint32_t k) {   // the batch's workers renew the labels
         const uint64_t w = __hip_atomic_load(reinterpret_cast<const uint64_t*>(part + k),
                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -209,8 +213,8 @@ __device__ __forceinline__ lp_share lp_share_of(const lp_part* part, const int32
     s.v0 = p0.v;
     s.v1 = max(p1.v, p0.v);
     s.cut = true;
-    s.e0 = (uint32_t)min(edges, lp_begin(edges, n, pieces, i) - p0.v);
-    s.e1 = (uint32_t)min(edges, lp_begin(edges, n, pieces, i + 1) - p1.v);
+    s.e0 = first + (uint32_t)min(edges, lp_begin(edges, n, pieces, i) - p0.v);
+    s.e1 = first + (uint32_t)min(edges, lp_begin(edges, n, pieces, i + 1) - p1.v);
     s.l0 = p0.label;
     s.l1 = p1.label;
     s.cont = (int32_t)s.e1 < rp[s.v1];
