@@ -324,8 +324,11 @@ hr_status hr_shadow_free(hr_ctx c, uint32_t region);
  * (hr_tn, hr_nested.h), as the instrumenter's launchers do.  The device
  * pointers in it stay owned by the context.
  * The block is valid until the next hr_kernel_end, hr_reset or region
- * change.  Errors: HR_E_INVAL (c NULL, out NULL, or cap too small: *size_out
- * still receives the size needed). */
+ * change.  The caller's kernel may run beside the launches before it on any
+ * stream, which a sweep (hr_jacobi_check) must not meet: if one was launched
+ * since the last hr_kernel_end, the call waits for it on the host.  Errors:
+ * HR_E_INVAL (c NULL, out NULL, or cap too small: *size_out still receives the
+ * size needed), HR_E_HIP. */
 hr_status hr_dev_args(hr_ctx c, void* out, size_t cap, size_t* size_out);
 
 /* Mark a kernel-launch boundary: every access of the launches before it
@@ -464,6 +467,11 @@ hr_status hr_word4_widen(uint32_t word, uint32_t wc_bits, uint32_t bc_bits, uint
  * kernel on `stream` (the caller calls hr_kernel_end after it); each *_plain
  * entry launches the same kernel without hooks.  Data pointers are device
  * pointers; region ids come from hr_shadow_alloc on those buffers.
+ * Launches between two hr_kernel_end calls may run beside each other on
+ * several streams, except that none runs beside a sweep (hr_jacobi_check) that
+ * was launched before it: `stream` waits for the sweep on the device.  Where
+ * that cannot be (the launch is recorded into a graph, or the sweep's stream
+ * has begun to record one), the call waits for it on the host.
  * Errors: HR_E_INVAL (bad sizes, regions too small), HR_E_HIP.
  * ---------------------------------------------------------------------- */
 

@@ -74,12 +74,14 @@ struct hr_ctx_s {
     uint32_t launch_seq;             // launches since the job started
     uint64_t shadow_bytes;           // live shadow memory
     std::vector<hr_race> carried;    // global races recovered before a shadow clear
-    // Launches of the current epoch (hr_epoch_enter): whether there are any,
-    // the stream of the last, whether several streams or the caller's own
-    // kernels (hr_dev_args) may take part, and whether one of them runs with
-    // env.excl.
-    bool epoch_used = false, epoch_shared = false, epoch_excl = false;
-    hipStream_t epoch_stream = nullptr;
+    // Checked launches of the current epoch (hr_epoch_enter): whether there are
+    // any, whether one was made elsewhere than on `stream`, whether the next
+    // one may run beside others, whether one of them runs with env.excl, and
+    // whether epoch_event lies behind those.
+    bool epoch_used = false, epoch_away = false, epoch_shared = false, epoch_excl = false;
+    bool epoch_recorded = false;
+    hipEvent_t epoch_event = nullptr;
+    bool recorded = false;           // a launch was recorded into a graph
     // Room for the pieces of a label-propagation launch (after the debug
     // counters, in their allocation): whether a launch ever used it, whether
     // one did since the job started, and the stream of the last.
@@ -90,13 +92,20 @@ struct hr_ctx_s {
 
 // Account for a checked launch on `s` in the current launch epoch.  *excl
 // (may be NULL: the kernel does not use it) receives the launch's env.excl:
-// every checked launch of the epoch so far was made on `s`, so none runs
-// beside it, and a later one will not either, since a launch on another
-// stream (or hr_dev_args) first waits here for the exclusive ones.  Neither
-// while `s` is being captured (a graph may be launched anywhere) nor on the
-// per-thread stream, whose handle names several streams: such a launch, too,
-// waits for the exclusive ones, and none after it in the epoch is.
+// no other checked launch of the epoch runs beside it.
+//
+// Those before it don't: all were made on the context's own stream, as this
+// one (`stream`, which outlives the context), or it is the epoch's first (another stream's
+// handle alone does not say that it is the stream of an earlier launch, which
+// may have been destroyed since).  Those after it don't either: one that is not
+// ordered behind it so waits for it first, on the device, or on the host where
+// it has no stream to wait on (hr_dev_args; a launch that is recorded, whose
+// graph may be replayed anywhere).  A graph may also be replayed at any later
+// time: after the first recorded launch of a context none is exclusive.  Nor
+// is one on the per-thread stream, whose handle names several streams.
 hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl);
+// The same launch has been made, with this env.excl.
+hr_status hr_epoch_leave(hr_ctx c, hipStream_t s, uint16_t excl);
 
 // Bytes of the counter words at the start of a context's counter-and-ring
 // allocation (the ring follows, 256-byte aligned).

@@ -298,6 +298,114 @@ void hr_fill_args(hr_ctx c, hr_kargs* a)
     }
 }
 
+namespace {
+
+// Calls that may wait or allocate while some stream records a graph.
+struct relaxed_capture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~relaxed_capture()
+    {
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+// Its launches run now, not as a graph's (false too if the handle is invalid).
+bool eager(hipStream_t s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Record `ev` (made on first use) behind the work launched on s so far.
+bool record(hipEvent_t& ev, hipStream_t s)
+{
+    const relaxed_capture r;
+    if ((ev || hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) &&
+        hipEventRecord(ev, s) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Let s wait on the device for an event.  (Refused for an event whose stream
+// has begun to record a graph since.)
+bool follow(hipStream_t s, hipEvent_t ev)
+{
+    const relaxed_capture r;
+    if (hipStreamWaitEvent(s, ev, 0) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Wait on the host for the work launched on the device so far, also while
+// streams record graphs: hipDeviceSynchronize and hipEventSynchronize would
+// end a recording, the wait that hipFree implies does not.
+hipError_t wait_device()
+{
+    const relaxed_capture r;
+    void* p = nullptr;
+    const hipError_t err = hipMalloc(&p, 256);
+    return err == hipSuccess ? hipFree(p) : err;
+}
+
+// From here on the epoch is shared.  What is launched next waits for its
+// exclusive launches: on stream s, or where there is none (the caller's own
+// kernels, a recorded launch) here on the host.
+hr_status epoch_share(hr_ctx c, const hipStream_t* s)
+{
+    c->epoch_shared = true;
+    if (!c->epoch_excl) return HR_OK;
+    const bool here = !c->epoch_away && eager(c->stream);   // launched on c->stream
+    if (!s && here) {
+        const relaxed_capture r;
+        if (hipStreamSynchronize(c->stream) != hipSuccess) return HR_E_HIP;
+        c->epoch_excl = false;
+        return HR_OK;
+    }
+    if (s && !c->epoch_recorded && here) c->epoch_recorded = record(c->epoch_event, c->stream);
+    if (s && c->epoch_recorded && follow(*s, c->epoch_event)) return HR_OK;
+    if (wait_device() != hipSuccess) return HR_E_HIP;
+    c->epoch_excl = false;
+    return HR_OK;
+}
+
+void epoch_begin(hr_ctx c)
+{
+    c->epoch_used = c->epoch_away = c->epoch_shared = c->epoch_excl = c->epoch_recorded = false;
+}
+
+}  // namespace
+
+hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
+{
+    const bool now = eager(s), one = now && s != hipStreamPerThread;
+    const bool home = one && s == c->stream;
+    if (!now) c->recorded = true;
+    const bool alone = one && !c->epoch_shared && (home ? !c->epoch_away : !c->epoch_used);
+    if (!alone) {
+        const hr_status st = epoch_share(c, now ? &s : nullptr);
+        if (st != HR_OK) return st;
+    }
+    c->epoch_used = true;
+    c->epoch_away |= !home;
+    if (excl) *excl = alone && !c->recorded;
+    return HR_OK;
+}
+
+hr_status hr_epoch_leave(hr_ctx c, hipStream_t s, uint16_t excl)
+{
+    if (!excl) return HR_OK;
+    if (s != c->stream) {
+        c->epoch_recorded = record(c->epoch_event, s);
+        if (!c->epoch_recorded) return wait_device() == hipSuccess ? HR_OK : HR_E_HIP;
+    }
+    c->epoch_excl = true;
+    return HR_OK;
+}
+
 // Wait for a stream's work, also while another stream records a graph; a stream
 // that records one itself is not waited for (hipErrorStreamCaptureUnsupported).
 // If its owner has destroyed the stream, wait for the device.
@@ -317,49 +425,9 @@ static hipError_t wait_for(hipStream_t s)
     return err != hipSuccess ? err : back;
 }
 
-// Wait for the exclusive launches of the epoch; from here on it is shared.  On
-// a stream that has begun to record a graph since, its earlier launches cannot
-// be waited for: the graph's come after them wherever it is replayed in their
-// order.
-static hr_status epoch_share(hr_ctx c)
-{
-    c->epoch_shared = true;
-    if (!c->epoch_excl) return HR_OK;
-    c->epoch_excl = false;
-    const hipError_t err = wait_for(c->epoch_stream);
-    return err == hipSuccess || err == hipErrorStreamCaptureUnsupported ? HR_OK : HR_E_HIP;
-}
-
-static void epoch_begin(hr_ctx c)
-{
-    c->epoch_used = c->epoch_shared = c->epoch_excl = false;
-}
-
-// A handle of one stream, whose launches run now and not as a graph's.
-static bool one_eager_stream(hipStream_t s)
-{
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    return s != hipStreamPerThread && hipStreamIsCapturing(s, &cap) == hipSuccess &&
-           cap == hipStreamCaptureStatusNone;
-}
-
-hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
-{
-    if (!one_eager_stream(s) || (c->epoch_used && c->epoch_stream != s)) {
-        const hr_status st = epoch_share(c);    // a graph may be replayed on any stream
-        if (st != HR_OK) return st;
-    }
-    c->epoch_used = true;
-    c->epoch_stream = s;
-    if (!excl) return HR_OK;
-    *excl = !c->epoch_shared;
-    c->epoch_excl |= *excl != 0;
-    return HR_OK;
-}
-
 lp_part* hr_lp_room(hr_ctx c, hipStream_t s)
 {
-    if (!one_eager_stream(s)) return nullptr;
+    if (!eager(s) || s == hipStreamPerThread) return nullptr;
     if (c->lp_any && c->lp_stream != s) {
         if (c->lp_used || wait_for(c->lp_stream) != hipSuccess) return nullptr;
     }
@@ -517,6 +585,7 @@ extern "C" hr_status hr_ctx_destroy(hr_ctx c)
     if (c->count) (void)hipFree(c->count);
     if (c->log) (void)hipFree(c->log);
     if (c->fsm_tab) (void)hipFree(c->fsm_tab);
+    if (c->epoch_event) (void)hipEventDestroy(c->epoch_event);
     delete c;
     return e == hipSuccess ? HR_OK : HR_E_HIP;
 }
@@ -574,7 +643,7 @@ extern "C" hr_status hr_dev_args(hr_ctx c, void* out, size_t cap, size_t* size_o
     if (!c) return HR_E_INVAL;
     if (size_out) *size_out = sizeof(hr_kargs);
     if (!out || cap < sizeof(hr_kargs)) return HR_E_INVAL;
-    const hr_status st = epoch_share(c);   // the caller's kernel may run on any stream
+    const hr_status st = epoch_share(c, nullptr);   // the caller's kernel may run on any stream
     if (st != HR_OK) return st;
     hr_fill_args(c, (hr_kargs*)out);
     return HR_OK;

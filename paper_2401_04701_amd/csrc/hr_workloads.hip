@@ -347,21 +347,23 @@ extern "C" hr_status hr_jacobi_check(hr_ctx c, uint32_t r_old, uint32_t r_new,
         return HR_E_INVAL;
     hr_kargs a;
     hr_fill_args(c, &a);
-    const hr_status st = hr_epoch_enter(c, hr_stream(c, stream), &a.env.excl);
+    if (!u_old_dev || !u_new_dev || !lay_fits(a, r_old, nx) || !lay_fits(a, r_new, nx))
+        return HR_E_INVAL;
+    const bool table = (c->cfg.flags & HR_CFG_FSM_TABLE) != 0;   // the row-major kernel only
+    if (table && (!c->fsm_tab || !lay_flat(a, r_old) || !lay_flat(a, r_new))) return HR_E_INVAL;
+    hipStream_t s = hr_stream(c, stream);
+    hr_status st = hr_epoch_enter(c, s, &a.env.excl);
     if (st != HR_OK) return st;
-    if (c->cfg.flags & HR_CFG_FSM_TABLE) {
-        // the transitions from the flat table: the row-major kernel only
-        if (!c->fsm_tab || !u_old_dev || !u_new_dev || !lay_flat(a, r_old) ||
-            !lay_flat(a, r_new) || !lay_fits(a, r_old, nx) || !lay_fits(a, r_new, nx))
-            return HR_E_INVAL;
+    if (table) {
+        // the transitions from the flat table
         auto k = (c->cfg.flags & HR_CFG_FSM_TABLE_LDS) ? k_jacobi_tab<1, true> : k_jacobi_tab<1>;
-        HR_LAUNCH(k, dim3((nx + 15) / 16, (ny + 15) / 16), dim3(256), 0, hr_stream(c, stream), a,
+        HR_LAUNCH(k, dim3((nx + 15) / 16, (ny + 15) / 16), dim3(256), 0, s, a,
                   gref(a, r_old, nx), gref(a, r_new, nx), u_old_dev, u_new_dev, ny, nx, seed_dev,
                   (const uint16_t*)c->fsm_tab);
-        return HR_OK;
+    } else {
+        st = hr_launch_jacobi(a, r_old, r_new, u_old_dev, u_new_dev, ny, nx, seed_dev, s);
     }
-    return hr_launch_jacobi(a, r_old, r_new, u_old_dev, u_new_dev, ny, nx, seed_dev,
-                            hr_stream(c, stream));
+    return st == HR_OK ? hr_epoch_leave(c, s, a.env.excl) : st;
 }
 
 hr_status hr_launch_jacobi(const hr_kargs& a, uint32_t r_old, uint32_t r_new,
