@@ -542,7 +542,11 @@ hr_status hr_jacobi_plain(const float* u_old_dev, float* u_new_dev, uint32_t ny,
  * row_ptr_dev[n] must not exceed the length of col_dev and mask_dev, which
  * is not checked (it lies in device memory).  Limits: 1 <= tpb <= 1024,
  * ceil(n / tpb) < 2^22 blocks.  HR_E_INVAL also for a context with
- * HR_CFG_NESTED_TILES or HR_CFG_FSM_TABLE. */
+ * HR_CFG_NESTED_TILES or HR_CFG_FSM_TABLE.  Checked sweeps of one context from
+ * 2,048 vertices on run one after another, on the device, also on several
+ * streams (they share the context's work room); recorded into a graph, or where
+ * `stream` cannot wait for the last one (its stream has begun to record), they
+ * run without that room, cut into equal ranges of vertices. */
 hr_status hr_labelprop_check(hr_ctx c, uint32_t r_label, uint32_t r_row_ptr, uint32_t r_col,
                              int32_t* label_dev, const int32_t* row_ptr_dev,
                              const int32_t* col_dev, const uint8_t* mask_dev, uint32_t n,

@@ -83,10 +83,10 @@ struct hr_ctx_s {
     hipEvent_t epoch_event = nullptr;
     bool recorded = false;           // a launch was recorded into a graph
     // Room for the pieces of a label-propagation launch (after the debug
-    // counters, in their allocation): whether a launch ever used it, whether
-    // one did since the job started, and the stream of the last.
-    bool lp_any = false, lp_used = false;
-    hipStream_t lp_stream = nullptr;
+    // counters, in their allocation): where it was last used, on `stream` or on
+    // another one, with lp_event recorded behind that launch.
+    enum { LP_NONE, LP_HOME, LP_AWAY } lp_last = LP_NONE;
+    hipEvent_t lp_event = nullptr;
     hr_host_buf h_ring, h_keys;      // hr_report's copy of the ring and its sort
 };
 
@@ -123,10 +123,11 @@ hr_env hr_env_of(const hr_config& cfg, hr_race_rec* ring, uint32_t* ctr,
 hr_env hr_make_env(hr_ctx c);
 void hr_fill_args(hr_ctx c, hr_kargs* a);
 // The context's room for the pieces of a label-propagation launch on `s`, or
-// NULL: a launch of this job on another stream may still use it, or `s` is
-// being captured or names several streams (see hr_epoch_enter).  A job's first
-// launch on another stream than the last job's waits for all launched work.
+// NULL: `s` is being captured or names several streams, or cannot wait for the
+// launch that uses the room (on the device; nothing waits on the host).  After
+// the launch: hr_lp_leave.
 lp_part* hr_lp_room(hr_ctx c, hipStream_t s);
+hr_status hr_lp_leave(hr_ctx c, hipStream_t s);
 // Bytes of that room.
 constexpr size_t HR_LP_ROOM_BYTES = (HR_LP_PIECES + 1) * 8;
 // A region usable through kernel arguments (id < HR_MAX_REGIONS), registered

@@ -406,34 +406,30 @@ hr_status hr_epoch_leave(hr_ctx c, hipStream_t s, uint16_t excl)
     return HR_OK;
 }
 
-// Wait for a stream's work, also while another stream records a graph; a stream
-// that records one itself is not waited for (hipErrorStreamCaptureUnsupported).
-// If its owner has destroyed the stream, wait for the device.
-static hipError_t wait_for(hipStream_t s)
-{
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return hipDeviceSynchronize();
-    }
-    if (cap != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    hipError_t err = hipThreadExchangeStreamCaptureMode(&mode);
-    if (err != hipSuccess) return err;
-    err = hipStreamSynchronize(s);
-    const hipError_t back = hipThreadExchangeStreamCaptureMode(&mode);
-    return err != hipSuccess ? err : back;
-}
-
 lp_part* hr_lp_room(hr_ctx c, hipStream_t s)
 {
-    if (!eager(s) || s == hipStreamPerThread) return nullptr;
-    if (c->lp_any && c->lp_stream != s) {
-        if (c->lp_used || wait_for(c->lp_stream) != hipSuccess) return nullptr;
-    }
-    c->lp_any = c->lp_used = true;
-    c->lp_stream = s;
+    if (s == hipStreamPerThread || !eager(s)) return nullptr;
+    const bool home = s == c->stream;
+    if (c->lp_last == hr_ctx_s::LP_HOME && !home &&
+        !(eager(c->stream) && record(c->lp_event, c->stream)))
+        return nullptr;
+    if ((c->lp_last == hr_ctx_s::LP_AWAY || (c->lp_last == hr_ctx_s::LP_HOME && !home)) &&
+        !follow(s, c->lp_event))
+        return nullptr;
+    if (home) c->lp_last = hr_ctx_s::LP_HOME;
     return (lp_part*)(c->count + HR_COUNT_SLOTS);
+}
+
+hr_status hr_lp_leave(hr_ctx c, hipStream_t s)
+{
+    if (s == c->stream) return HR_OK;
+    if (record(c->lp_event, s)) {
+        c->lp_last = hr_ctx_s::LP_AWAY;
+        return HR_OK;
+    }
+    if (wait_device() != hipSuccess) return HR_E_HIP;
+    c->lp_last = hr_ctx_s::LP_NONE;
+    return HR_OK;
 }
 
 bool hr_region_ok(hr_ctx c, uint32_t r, const void* data, size_t min_elems)
@@ -586,6 +582,7 @@ extern "C" hr_status hr_ctx_destroy(hr_ctx c)
     if (c->log) (void)hipFree(c->log);
     if (c->fsm_tab) (void)hipFree(c->fsm_tab);
     if (c->epoch_event) (void)hipEventDestroy(c->epoch_event);
+    if (c->lp_event) (void)hipEventDestroy(c->lp_event);
     delete c;
     return e == hipSuccess ? HR_OK : HR_E_HIP;
 }
@@ -739,7 +736,6 @@ extern "C" hr_status hr_reset(hr_ctx c, void* stream)
     c->launch_seq = 0;
     c->carried.clear();
     epoch_begin(c);
-    c->lp_used = false;
     return HR_OK;
 }
 

@@ -418,6 +418,20 @@ static bool labelprop_shape_ok(uint32_t n, uint32_t tpb)
     return (uint64_t)(n + tpb - 1) / tpb < hr::g::BLOCK_LIMIT;
 }
 
+// Pieces of a launch over n vertices (0: cut by vertices).  Jobs of 10
+// launches, 8 edges a vertex, in us: below 2,048 vertices the launch that cuts
+// costs more than it gives (1,000 vertices 249 cut by vertices, 264 in
+// pieces; 2,000 vertices 312 and 270).  Smaller pieces balance better, but
+// every block in flight can find a hub's word unsettled: 8,200 vertices 330
+// with 64 pieces, 406 with 16; 32,800: 468 with 128, 494 with 256; 100,003:
+// 688 with 195, 830 with 781; 2^20: 2,130 with 1,024, 2,240 with 2,048.
+static uint32_t labelprop_pieces(uint32_t n)
+{
+    if (n < 2048) return 0;
+    return std::min(HR_LP_PIECES,
+                    std::max({std::min(n / 128, 96u), std::min(n / 512, 256u), n / 1024}));
+}
+
 extern "C" hr_status hr_labelprop_check(hr_ctx c, uint32_t r_label, uint32_t r_row_ptr,
                                         uint32_t r_col, int32_t* label_dev,
                                         const int32_t* row_ptr_dev, const int32_t* col_dev,
@@ -434,11 +448,14 @@ extern "C" hr_status hr_labelprop_check(hr_ctx c, uint32_t r_label, uint32_t r_r
     if (r_col != UINT32_MAX && !hr_region_ok(c, r_col, col_dev, 1)) return HR_E_INVAL;
     hr_kargs a;
     hr_fill_args(c, &a);
-    const hr_status st = hr_epoch_enter(c, hr_stream(c, stream), nullptr);
+    hipStream_t s = hr_stream(c, stream);
+    hr_status st = hr_epoch_enter(c, s, nullptr);
     if (st != HR_OK) return st;
-    return hr_launch_labelprop(a, r_label, r_row_ptr, r_col, label_dev, row_ptr_dev, col_dev,
-                               mask_dev, n, tpb, hr_lp_room(c, hr_stream(c, stream)),
-                               hr_stream(c, stream));
+    lp_part* room = labelprop_pieces(n) && !a.env.group ? hr_lp_room(c, s) : nullptr;
+    st = hr_launch_labelprop(a, r_label, r_row_ptr, r_col, label_dev, row_ptr_dev, col_dev,
+                             mask_dev, n, tpb, room, s);
+    const hr_status left = room ? hr_lp_leave(c, s) : HR_OK;
+    return st == HR_OK ? left : st;
 }
 
 // Vertices per 1024-thread block where the blocks are cut by vertices: about
@@ -453,20 +470,6 @@ static uint32_t labelprop_vertices_per_block(uint32_t n)
     while (vb < 256 && n / vb > 4096) vb *= 2;
     while ((n - 1) / vb + 1 >= (1u << 22)) vb *= 2;   // a grid holds below 2^32 threads
     return vb;
-}
-
-// Pieces of a launch over n vertices (0: cut by vertices).  Jobs of 10
-// launches, 8 edges a vertex, in us: below 2,048 vertices the launch that cuts
-// costs more than it gives (1,000 vertices 249 cut by vertices, 264 in
-// pieces; 2,000 vertices 312 and 270).  Smaller pieces balance better, but
-// every block in flight can find a hub's word unsettled: 8,200 vertices 330
-// with 64 pieces, 406 with 16; 32,800: 468 with 128, 494 with 256; 100,003:
-// 688 with 195, 830 with 781; 2^20: 2,130 with 1,024, 2,240 with 2,048.
-static uint32_t labelprop_pieces(uint32_t n)
-{
-    if (n < 2048) return 0;
-    return std::min(HR_LP_PIECES,
-                    std::max({std::min(n / 128, 96u), std::min(n / 512, 256u), n / 1024}));
 }
 
 // check: 0 plain, 1 checked, 2 checked with the access log.  part: room for

@@ -212,3 +212,40 @@ def test_a_sweep_on_a_second_stream_returns_at_once(env):
     done = time.perf_counter() - t
     assert done > 0.02 and called < done / 3
     j.ctx.close()
+
+
+def test_label_propagation_on_a_second_stream_returns_at_once(env):
+    """One job after the other on two streams, and both streams in one job."""
+    torch, hr = env
+    print("[case] epoch waits, asynchronous label propagation", flush=True)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(a):
+        ctx = hr.Context()
+        n = 4000
+        rp = torch.arange(n + 1, dtype=torch.int32, device="cuda")
+        col = torch.arange(1, n + 1, dtype=torch.int32, device="cuda") % n
+        mask = torch.zeros(n, dtype=torch.uint8, device="cuda")
+        label = torch.arange(n, dtype=torch.int32, device="cuda")
+        r = ctx.shadow_alloc(label)
+
+    def sweep(s):
+        ctx.labelprop_check(r, label, rp, col, mask, stream=s)
+        ctx.kernel_end(stream=s)
+
+    def jobs(busy):
+        with torch.cuda.stream(a):
+            torch.cuda._sleep(busy)
+        for s in (a, b, a):
+            ctx.reset(stream=s)
+            sweep(s)
+        sweep(b)
+
+    jobs(1000)
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    jobs(400_000_000)
+    called = time.perf_counter() - t
+    torch.cuda.synchronize()
+    done = time.perf_counter() - t
+    assert done > 0.02 and called < done / 3
+    ctx.close()
