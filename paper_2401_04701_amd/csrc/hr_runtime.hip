@@ -4,7 +4,6 @@
 
 #include <algorithm>
 #include <cstring>
-#include <initializer_list>
 #include <new>
 #include <vector>
 
@@ -62,18 +61,25 @@ __global__ __launch_bounds__(256) void k_clear_word4(segs g, const uint32_t* __r
     }
 }
 
-// Launch `kern` over pieces of memory, SEGS at a time.
+// Launch `kern` over pieces of memory, SEGS at a time: head[0 .. n_head), then
+// the shadow allocations of c (may be null).  Nothing is allocated.
 template <class K, class... A>
-hipError_t launch_segs(K kern, const hr_piece* pieces, size_t count, hipStream_t s, A... args)
+hipError_t launch_segs(K kern, hr_ctx c, const hr_piece* head, size_t n_head, hipStream_t s,
+                       A... args)
 {
-    for (size_t at = 0; at < count;) {
+    const size_t n = n_head + (c ? c->allocs.size() : 0);
+    for (size_t at = 0; at < n;) {
         segs g{};
         size_t most = 0;
-        for (; at < count && g.count < SEGS; ++at) {
-            if (pieces[at].words == 0) continue;
-            g.p[g.count] = (uint64_t*)pieces[at].mem;
-            g.n[g.count++] = pieces[at].words;
-            most = std::max(most, pieces[at].words);
+        for (; at < n && g.count < SEGS; ++at) {
+            hr_piece p{nullptr, 0};
+            if (at < n_head) p = head[at];
+            else if (c->allocs[at - n_head].live)
+                p = {c->allocs[at - n_head].mem, c->allocs[at - n_head].words};
+            if (p.words == 0) continue;
+            g.p[g.count] = (uint64_t*)p.mem;
+            g.n[g.count++] = p.words;
+            most = std::max(most, p.words);
         }
         if (g.count == 0) break;
         const size_t blocks = std::min<size_t>((most + 511) / 512, 4096);
@@ -83,15 +89,6 @@ hipError_t launch_segs(K kern, const hr_piece* pieces, size_t count, hipStream_t
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-// The shadow allocations of a context, after `head`.
-std::vector<hr_piece> shadow_pieces(hr_ctx c, std::initializer_list<hr_piece> head = {})
-{
-    std::vector<hr_piece> v(head);
-    for (const hr_alloc& al : c->allocs)
-        if (al.live) v.push_back({al.mem, al.words});
-    return v;
 }
 
 // The global races among n shadow words: each word in the race state is
@@ -247,7 +244,7 @@ hipError_t hr_scan_races_dev(const uint64_t* sh, size_t n, size_t first, bool wo
 // inside a captured HIP graph.
 hipError_t hr_fill(const hr_piece* pieces, size_t count, hipStream_t s)
 {
-    return launch_segs(k_fill, pieces, count, s);
+    return launch_segs(k_fill, nullptr, pieces, count, s);
 }
 
 hipStream_t hr_stream(hr_ctx c, void* stream)
@@ -697,8 +694,7 @@ extern "C" hr_status hr_kernel_end(hr_ctx c, void* stream)
     if (c->cfg.flags & HR_CFG_WORD4) {
         // No launch field: every boundary returns the words to INIT.
         hipStream_t s = hr_stream(c, stream);
-        const std::vector<hr_piece> v = shadow_pieces(c);
-        if (launch_segs(k_clear_word4, v.data(), v.size(), s, (const uint32_t*)c->ctr,
+        if (launch_segs(k_clear_word4, c, nullptr, 0, s, (const uint32_t*)c->ctr,
                         c->cfg.ring_capacity) != hipSuccess)
             return HR_E_HIP;
         return HR_OK;
@@ -719,9 +715,7 @@ extern "C" hr_status hr_kernel_end(hr_ctx c, void* stream)
             const hr_status st = scan_races(c, c->carried);
             if (st != HR_OK) return st;
         }
-        const std::vector<hr_piece> v = shadow_pieces(c);
-        if (hr_fill(v.data(), v.size(), s) != hipSuccess) return HR_E_HIP;
-        return HR_OK;
+        return launch_segs(k_fill, c, nullptr, 0, s) == hipSuccess ? HR_OK : HR_E_HIP;
     }
     return HR_OK;
 }
@@ -730,9 +724,8 @@ extern "C" hr_status hr_reset(hr_ctx c, void* stream)
 {
     if (!c) return HR_E_INVAL;
     hipStream_t s = hr_stream(c, stream);
-    const std::vector<hr_piece> v =
-        shadow_pieces(c, {HR_CTR_PIECE(c->ctr), {c->count, HR_COUNT_SLOTS}});
-    if (hr_fill(v.data(), v.size(), s) != hipSuccess) return HR_E_HIP;
+    const hr_piece head[] = {HR_CTR_PIECE(c->ctr), {c->count, HR_COUNT_SLOTS}};
+    if (launch_segs(k_fill, c, head, 2, s) != hipSuccess) return HR_E_HIP;
     c->launch_seq = 0;
     c->carried.clear();
     epoch_begin(c);
