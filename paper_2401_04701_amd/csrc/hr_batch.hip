@@ -36,7 +36,9 @@ __device__ __forceinline__ uint64_t claim(uint32_t* cursor, const uint64_t* item
 // and a later one reads (cells, labels, shadow words, pieces' labels) is
 // written and read with agent-scope operations, which act past the L2s of
 // the chip's dies, so a phase is complete for the others once its waves'
-// stores are (this wait) and the counter then says so.  A release and an
+// stores are (this wait) and the counter then says so.  (The general hook
+// alone loads its word through the caches, also a state of an earlier phase:
+// its exchange and fold make up for that, hr_check_any.)  A release and an
 // acquire at agent scope per item, which write back and invalidate a whole
 // L2 under the 31 workers beside it, made a stencil item of four tiles 33 us
 // and a label-propagation item 100 us.

@@ -483,11 +483,12 @@ __device__ __forceinline__ void hr_check_any(const hr_env& e, const hr_thread& t
         other = hr_group((uint64_t)sp >> 3 | (uint64_t)kind << 60, e.group, &member);
         if (member) return;
     }
-    // A cached load: any earlier state of the word in this launch will do
-    // (tests/test_stale.py).  A state that the access does not change holds
-    // it, and so do all later ones; from any other one the exchange and the
-    // fold make the word's state of it, as for an update that lands between
-    // load and exchange.  Words that many threads share settle early and are
+    // A cached load: any earlier state of the word will do, of this launch or
+    // (between the phases of a batch) of an earlier one (tests/test_hooks.py).
+    // A state that the access does not change holds it, and so do all later
+    // ones of the launch; from any other one the exchange and the fold make
+    // the word's state of it, as for an update that lands between load and
+    // exchange (hr::g::merge).  Words that many threads share settle early and are
     // then read from the caches: a histogram of 1.5 M keys in 4,096 bins, both
     // monitored, 245 to 230 us (154 unmonitored).
     const uint64_t old =

@@ -272,12 +272,16 @@ HR_HD uint64_t step_tab(const uint16_t* tab, uint64_t old, uint64_t id, uint32_t
 // Summary of the union of the access sets summarised by x and y, where x
 // belongs to the current launch (an initial y, or one of another launch,
 // adds nothing).  Used to fold
-// back an update that a concurrent exchange overwrote.  Exact under the
-// condition the hook guarantees: every access in one summary but not the
-// other either comes from another block (then the union spans >= 2 blocks)
-// or lies in the latest block epoch, and within one wave in the latest wave
-// epoch, of both summaries, because a thread still inside its hook holds
-// back its own block and wave barriers.  With accesses from >= 2 blocks
+// back an update that a concurrent exchange overwrote.  x may have been
+// stepped from any earlier state of the word (a load that came early, from a
+// cache, or not at all), so each may lack accesses of the other.  Exact where
+// of one block's accesses those in the latest block epoch of the union, and of
+// one wave's those in its latest wave epoch, are each in the details of a
+// summary whose own latest epoch it is: an older epoch's accesses add their
+// classes only.  A summary keeps just those details, and a thread inside its
+// hook holds back its own block and wave barriers, so no access of a later
+// epoch of its block (wave) comes before its fold ends
+// (tests/test_hooks.py).  With accesses from >= 2 blocks
 // (or waves, or threads) in the same scope and epoch, the union is free of
 // races exactly when all of it has one class, R or A.
 HR_HD uint64_t merge(uint64_t x, uint64_t y, uint64_t wm = WAVE_M)
