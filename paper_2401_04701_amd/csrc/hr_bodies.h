@@ -140,9 +140,9 @@ struct lp_part {
 
 // Vertex v's edges are row_ptr[v] .. row_ptr[v + 1]; in a range of a larger
 // graph's rows row_ptr[0] is not 0.  lp_edge: the edges before vertex v's.
-__device__ __forceinline__ uint64_t lp_edge(const int32_t* __restrict__ rp, uint64_t v)
+__device__ __forceinline__ uint32_t lp_edge(const int32_t* __restrict__ rp, uint64_t v)
 {
-    return (uint64_t)max((int64_t)rp[v] - rp[0], (int64_t)0);
+    return (uint32_t)max(rp[v], rp[0]) - (uint32_t)rp[0];
 }
 
 // The first position of piece i when n vertices and `edges` edges are cut
