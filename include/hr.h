@@ -358,8 +358,11 @@ hr_status hr_reset(hr_ctx c, void* stream);
  * site_limit) the global-memory part of the set is completed from the sticky
  * race states in shadow memory (those records carry HR_RACE_SCANNED).
  * Returns the warning bits, HR_E_INVAL (c or n_out NULL, or cap too small:
- * *n_out then holds the count), or HR_E_HIP.  The ring is not cleared (see
- * hr_reset). */
+ * *n_out then holds the count), HR_E_NOMEM or HR_E_HIP.  The ring is not
+ * cleared (see hr_reset).  The context keeps the host memory of its largest
+ * report until it is destroyed: 80 bytes per record of the ring that was
+ * copied, so at most 80 * ring_capacity (more only for a set completed from
+ * shadow memory: 32 bytes per record of it). */
 hr_status hr_report(hr_ctx c, hr_race* out, size_t cap, size_t* n_out, void* stream);
 
 /* Synchronise `stream` and read the checked-access counter (only counts when
@@ -672,8 +675,8 @@ hr_status hr_job_run(const hr_instance* inst, const hr_config* cfg, hr_race* out
  * allocation): the same job, launches and report, but the counters, the
  * report ring (at most HR_STATIC_RING_RECORDS records; a larger
  * cfg->ring_capacity is capped) and the shadow words live in one static
- * device array of HR_STATIC_SCRATCH_BYTES (and 32 KiB of work room behind
- * them) that the library holds on each
+ * device array of HR_STATIC_SCRATCH_BYTES (and 32,776 bytes of work room
+ * behind them) that the library holds on each
  * device it runs on until the process ends.  The call allocates nothing, on
  * the device or through any allocating library routine; it clears the parts
  * of the array it uses before the first launch, so nothing of an earlier

@@ -222,7 +222,7 @@ __device__ __forceinline__ lp_share lp_share_of(const lp_part* part, const int32
 }
 
 // What bounds it: whole lines read for one label or one shadow word of an
-// edge's target (2^25 edges: 3.3 GB per launch, 4.5 times the words that the
+// edge's target (2^25 edges: 3.2 GB per launch, 4.4 times the words that the
 // sweep needs, at 4.3 TB/s), and in smaller graphs the hubs' words: until the first update of a
 // hub's word lands, every lane with an edge into the hub exchanges the word,
 // and exchanges of one word run one after another.  So in the blocks that

@@ -77,13 +77,15 @@ struct hr_tile_sync {
 // kernel whose blocks run several sweeps with only a counter between them.
 //
 // What bounds it: memory.  4096 x 4096: 0.129 ms per launch, 5.2 TB/s of the
-// 671 MB of grids and shadow words (a large copy reaches 4.9 to 5.8 TB/s
-// here), against 0.278 ms with every access published by its own thread's exchange
+// 671 MB of grids and shadow words (copies of 0.5 to 8 GiB reach 4.5 to 5.6
+// TB/s here, smaller ones up to 6.8 with the memory-side cache), against 0.278 ms with every access published by its own thread's exchange
 // (100 memory-side requests per tile, which run at 25 G/s on the chip, and
 // 530 vector instructions per wave).  The general transitions in place of
 // the closed forms (hr_own_fast), with their rare paths inside the kernel
 // and not at its end, took 0.184 ms, issue-bound; plain, nontemporal or
-// coherent loads and stores of the words made no difference.
+// coherent loads and stores of the words made no difference.  A launch that
+// is not alone in its epoch (no env.excl) leaves every word to the general
+// transitions and an exchange: 0.200 ms.
 template <int CHECK, class G = hr_gref, class SYNC = hr_block_sync, bool COH = false>
 __device__ __forceinline__ void jacobi_body(const hr_env& e, const G& gold, const G& gnew,
                             const float* __restrict__ uo, float* __restrict__ un, uint32_t ny,
