@@ -103,7 +103,8 @@ struct hr_ctx_s {
 // graph may be replayed anywhere).  A graph may also be replayed at any later
 // time: after the first recorded launch of a context none is exclusive.  Nor
 // is one on the per-thread stream, whose handle names several streams.
-hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl);
+// away: whether it may be exclusive on another stream than the context's.
+hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl, bool away = true);
 // The same launch has been made, with this env.excl.
 hr_status hr_epoch_leave(hr_ctx c, hipStream_t s, uint16_t excl);
 

@@ -376,7 +376,7 @@ void epoch_begin(hr_ctx c)
 
 }  // namespace
 
-hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
+hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl, bool away)
 {
     const bool now = eager(s), one = now && s != hipStreamPerThread;
     const bool home = one && s == c->stream;
@@ -388,7 +388,7 @@ hr_status hr_epoch_enter(hr_ctx c, hipStream_t s, uint16_t* excl)
     }
     c->epoch_used = true;
     c->epoch_away |= !home;
-    if (excl) *excl = alone && !c->recorded;
+    if (excl) *excl = alone && !c->recorded && (home || away);
     return HR_OK;
 }
 

@@ -336,6 +336,14 @@ static bool jacobi_shape_ok(uint32_t ny, uint32_t nx)
     return nby <= 65535 && nbx <= 65535 && nbx * nby < hr::g::BLOCK_LIMIT;
 }
 
+// From how many cells on a sweep on another stream than the context's is
+// exclusive: the event behind it (hr_epoch_leave) costs about 3 us, an exchange
+// per word 8 ns for every 1,000 cells (4-byte words 6).  Per launch, exclusive
+// and not, in us: 300 x 300 9.6 and 6.8, 513 x 777 10.2 and 10.7, 600 x 900 10.7 and
+// 12.3, 1500 x 1500 20.1 and 35.6; 4-byte words 513 x 777 15.0 and 12.9,
+// 1024 x 1024 18.7 and 18.9, 1500 x 1500 27.7 and 37.8.
+static size_t sweep_away_cells(bool word4) { return word4 ? 1u << 20 : 3u << 17; }
+
 extern "C" hr_status hr_jacobi_check(hr_ctx c, uint32_t r_old, uint32_t r_new,
                                      const float* u_old_dev, float* u_new_dev, uint32_t ny,
                                      uint32_t nx, const int32_t* seed_dev, void* stream)
@@ -352,7 +360,7 @@ extern "C" hr_status hr_jacobi_check(hr_ctx c, uint32_t r_old, uint32_t r_new,
     const bool table = (c->cfg.flags & HR_CFG_FSM_TABLE) != 0;   // the row-major kernel only
     if (table && (!c->fsm_tab || !lay_flat(a, r_old) || !lay_flat(a, r_new))) return HR_E_INVAL;
     hipStream_t s = hr_stream(c, stream);
-    hr_status st = hr_epoch_enter(c, s, &a.env.excl);
+    hr_status st = hr_epoch_enter(c, s, &a.env.excl, cells >= sweep_away_cells(a.env.word4 != 0));
     if (st != HR_OK) return st;
     if (table) {
         // the transitions from the flat table
